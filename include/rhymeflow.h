@@ -160,7 +160,7 @@ int rf_project_latents(const void *latents, void *out, const double timesteps[3]
  * and Rhythmic Points, Sec. 3.2.1, 3.2.3).
  * head_dim: 64 or 128. dtype: RF_BF16 (bf16 inputs and output, bf16 matrix
  *          cores, fp32 softmax and accumulation, output rounded to nearest
- *          even) or RF_F32 (fp32 throughout, a correctness path).
+ *          even) or RF_F32 (fp32 inputs, products, sums and output throughout).
  * Errors: RF_ERR_INVALID_ARG (NULL, sizes <= 0, ids not strictly increasing,
  *         out overlapping an input), RF_ERR_RANGE (an id outside [0, T), M > T,
  *         T > RF_MAX_FRAMES, sizes whose byte counts would pass 4e18),
@@ -186,7 +186,10 @@ int rf_keyframe_attention(const void *q, const void *k, const void *v, void *out
  * workspace: device, 16-byte aligned, at least rf_attention_workspace bytes
  *   for the current device's compute units (compute_units = 0 there) (may be
  *   0: then nothing is split), not overlapping q, k, v or out; its
- *   contents are overwritten and meaningless afterwards. fp32 ignores it.
+ *   contents are overwritten and meaningless afterwards. fp32 needs and
+ *   touches none of it, but a small fp32 launch given one shares out the keys
+ *   of each query tile among the waves of a workgroup (the same effect on
+ *   the order of its sums).
  * Other arguments and errors as rf_keyframe_attention; RF_ERR_INVALID_ARG also
  * for a NULL or too small workspace or an overlap.
  */

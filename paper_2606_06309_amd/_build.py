@@ -17,7 +17,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "librhymeflow.so")
 ARCH = "gfx950"
 
-SOURCES = ["rf_abi.cpp", "rf_attention.hip", "rf_project.hip", "rf_gather.hip", "rf_similarity.hip",
+SOURCES = ["rf_abi.cpp", "rf_attention.hip", "rf_attention_f32.hip", "rf_project.hip", "rf_gather.hip", "rf_similarity.hip",
            "rf_cache.hip", "rf_probe.hip", "rf_noalloc.hip"]
 
 HIPCC_FLAGS = [

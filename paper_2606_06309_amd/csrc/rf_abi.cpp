@@ -285,12 +285,10 @@ static int attention_call(const void *q, const void *k, const void *v, void *out
                              overlaps(ws, ws_bytes, v, in_bytes) || overlaps(ws, ws_bytes, out, out_bytes)))
             return fail(RF_ERR_INVALID_ARG, "%s: workspace overlaps q, k, v or out", fn);
     }
-    // every argument is valid: the bf16 split plan and tile order follow the device
-    p.geo.cus = p.geo.xcds = 1;
-    if (dtype == RF_BF16) {
-        rc = query_geometry(&p.geo, fn);
-        if (rc != RF_OK) return rc;
-    }
+    // every argument is valid: the split plan and tile order follow the device
+    rc = query_geometry(&p.geo, fn);
+    if (rc != RF_OK) return rc;
+    p.split_keys = use_scratch || ws != nullptr;
     if (use_scratch) {
         const int64_t need = attention_ws_need(M, n_kv, T, N, heads, head_dim, dtype, p.geo.cus);
         if (need > rf::kAttentionScratchBytes)

@@ -53,10 +53,10 @@
 //    h = fmaf(alpha, h_after, (1 - alpha) h_before), rounded once to bf16, in
 //    LDS as both the key tile and the value tile, so the projected keys and
 //    values are never written to HBM.
-// The fp32 kernel at the end is a plain correctness path (fp32 throughout).
+// The fp32 kernels are in rf_attention_f32.hip.
 #include <atomic>
 
-#include "rf_internal.h"
+#include "rf_device.h"
 
 namespace rf {
 namespace {
@@ -153,19 +153,6 @@ constexpr int kFormDense = 0;    // all S tokens in order
 constexpr int kFormFrames = 1;   // the tokens of the listed frames a.kvf
 constexpr int kFormCache = 2;    // all frames; cached frames give projected keys = values
 
-// Word 3 of a raw (untyped, stride 0) buffer resource on gfx9-class GPUs.
-constexpr int kBufferWord3 = 0x00020000;
-
-__device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// A pointer every lane holds the same value of, rebuilt from its first lane.
-__device__ __forceinline__ void *uniform_ptr(const void *p) {
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
-    return reinterpret_cast<void *>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
 // Two floats -> two bf16 (round to nearest even) packed low-first in a word.
 __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
     const bf16x2_t v = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
@@ -178,17 +165,6 @@ __device__ inline bf16x8_t as_bf16x8(u32x4_t w) { return __builtin_bit_cast(bf16
 __device__ __forceinline__ float add_bf16x2(uint32_t word, float acc) {
     const bf16x2_t one = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, word), one, acc, false);
-}
-
-// Combine the values of lanes l and l ^ 32 with one VALU swap of the wave
-// halves: r[0] holds lanes 0..31 in both halves, r[1] lanes 32..63.
-__device__ __forceinline__ float halves_max(float x) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float halves_sum(float x) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // LDS tile layout. A tile holds kBc keys of one head, K and V each in natural
@@ -215,16 +191,7 @@ struct TileLayout {
 };
 
 typedef short i16x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(3))) i16x4_t lds_i16x4_t;
-
-// 16 bytes per lane from a buffer resource straight into LDS: lane l's bytes
-// land at dst + 16 l; offsets at or past the resource's range read as zero.
-// (Kept out of the kernel template: the host pass drops the launch stub of a
-// template that names this builtin.)
-__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, lds_void_t *dst, int voffset) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, voffset, 0, 0, 0);
-}
 
 // S^T = K Q^T for one tile of kNB 32-key blocks. kofs[kk] is this lane's byte
 // offset of its K fragment for reduction step kk inside block 0. The K
@@ -728,104 +695,6 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(const Com
     *reinterpret_cast<u32x4_t *>(a.out + row * rs + static_cast<int64_t>(head) * D + c8 * 8) = w;
 }
 
-// ---------------------------------------------------------------------------
-// fp32 path: a correctness path with fp32 arithmetic throughout. A workgroup
-// of 128 lanes owns 64 query rows of one head; each row is shared by two
-// adjacent lanes that each hold half of the head dimension.
-// ---------------------------------------------------------------------------
-
-constexpr int kF32Rows = 64;
-constexpr int kF32Keys = 32;
-
-struct AttnF32Args {
-    const float *q;
-    const float *k;
-    const float *v;
-    float *out;
-    int64_t S;
-    int64_t N;
-    int64_t Mq;
-    int32_t heads;
-    float scale;       // 1 / sqrt(d)
-    int32_t kf[kMaxFrames];
-    int32_t n_kv;      // > 0: the keys are the tokens of frames kvf[0..n_kv), S = n_kv * N
-    int32_t kvf[kMaxFrames];
-};
-
-template <int D>
-__global__ __launch_bounds__(2 * kF32Rows) void attn_f32_kernel(const AttnF32Args a) {
-    constexpr int HD = D / 2;
-    __shared__ float ks[kF32Keys][D];
-    __shared__ float vs[kF32Keys][D];
-    const int head = blockIdx.y;
-    const int tid = threadIdx.x;
-    const int half = tid & 1;
-    const int64_t row = static_cast<int64_t>(blockIdx.x) * kF32Rows + (tid >> 1);
-    const int64_t rs = static_cast<int64_t>(a.heads) * D;
-
-    float qv[HD], o[HD];
-    if (row < a.Mq) {
-        const int64_t f = row / a.N;
-        const int64_t tok = static_cast<int64_t>(a.kf[f]) * a.N + (row - f * a.N);
-        const float *qp = a.q + tok * rs + static_cast<int64_t>(head) * D + half * HD;
-#pragma unroll
-        for (int c = 0; c < HD; ++c) qv[c] = qp[c];
-    } else {
-#pragma unroll
-        for (int c = 0; c < HD; ++c) qv[c] = 0.0f;
-    }
-#pragma unroll
-    for (int c = 0; c < HD; ++c) o[c] = 0.0f;
-    float m = -__builtin_huge_valf(), l = 0.0f;
-
-    for (int64_t j0 = 0; j0 < a.S; j0 += kF32Keys) {
-        __syncthreads();
-        for (int i = tid; i < kF32Keys * D; i += 2 * kF32Rows) {
-            const int key = i / D, c = i % D;
-            const int64_t j = j0 + key;
-            int64_t tok = j;
-            if (a.n_kv > 0 && j < a.S) {
-                const int64_t m = j / a.N;
-                tok = static_cast<int64_t>(a.kvf[m]) * a.N + (j - m * a.N);
-            }
-            const int64_t off = tok * rs + static_cast<int64_t>(head) * D + c;
-            ks[key][c] = j < a.S ? a.k[off] : 0.0f;
-            vs[key][c] = j < a.S ? a.v[off] : 0.0f;
-        }
-        __syncthreads();
-        float s[kF32Keys];
-        float mt = -__builtin_huge_valf();
-#pragma unroll
-        for (int jj = 0; jj < kF32Keys; ++jj) {
-            float part = 0.0f;
-#pragma unroll
-            for (int c = 0; c < HD; ++c) part = fmaf(qv[c], ks[jj][half * HD + c], part);
-            const float dot = part + __shfl_xor(part, 1);
-            s[jj] = (j0 + jj < a.S) ? dot * a.scale : -__builtin_huge_valf();
-            mt = fmaxf(mt, s[jj]);
-        }
-        const float m_new = fmaxf(m, mt);
-        const float corr = expf(m - m_new);
-        l *= corr;
-#pragma unroll
-        for (int c = 0; c < HD; ++c) o[c] *= corr;
-#pragma unroll
-        for (int jj = 0; jj < kF32Keys; ++jj) {
-            const float p = expf(s[jj] - m_new);
-            l += p;
-#pragma unroll
-            for (int c = 0; c < HD; ++c) o[c] = fmaf(p, vs[jj][half * HD + c], o[c]);
-        }
-        m = m_new;
-    }
-    if (row < a.Mq) {
-        float *op = a.out + row * rs + static_cast<int64_t>(head) * D + half * HD;
-        const float inv = 1.0f / l;
-#pragma unroll
-        for (int c = 0; c < HD; ++c) op[c] = o[c] * inv;
-    }
-}
-
 }  // namespace
 
 hipError_t device_geometry(DeviceGeometry *out) {
@@ -885,107 +754,86 @@ AttnSplit attention_split(int64_t Mq, int32_t heads, int32_t head_dim, int64_t N
 
 hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {
     const int64_t Mq = static_cast<int64_t>(p.M) * p.N;
-    if (p.dtype == RF_BF16) {
-        AttnKArgs a{};
-        a.q = static_cast<const uint16_t *>(p.q);
-        a.k = static_cast<const uint16_t *>(p.k);
-        a.v = static_cast<const uint16_t *>(p.v);
-        a.out = static_cast<uint16_t *>(p.out);
-        a.S = p.S;
-        a.N = p.N;
-        a.Mq = Mq;
-        a.heads = p.heads;
-        const int64_t nq = (Mq + kBr - 1) / kBr;
-        const int32_t xcds = p.geo.xcds;
-        if (p.geo.cus < 1 || xcds < 1 || xcds > 64) return hipErrorInvalidValue;
-        AttnSplit sp{};
-        sp.n_direct = nq * p.heads;
-        const int32_t walk = p.cache_form ? static_cast<int32_t>(p.S / p.N) : 0;
-        if (p.ws) {
-            sp = attention_split(Mq, p.heads, p.head_dim, p.N, p.S, p.n_kv, p.geo.cus, walk);
-            if (sp.split > 0 && p.ws_bytes < sp.ws_bytes) return hipErrorInvalidValue;
-        }
-        const int64_t total = sp.n_direct;
-        const int64_t per_xcd = (total + xcds - 1) / xcds;
-        if (nq * p.heads > 0x7fffffffLL / 64) return hipErrorInvalidConfiguration;
-        // per-lane load offsets inside a tile are 32-bit: a tile's token rows must span < 2 GiB
-        const int64_t kBc = key_tile(p.head_dim);
-        if (static_cast<int64_t>(p.heads) * p.head_dim * 2 * kBc >= 0x7fffffffLL) return hipErrorInvalidConfiguration;
-        a.n_qtiles = static_cast<int32_t>(nq);
-        a.total_tiles = static_cast<int32_t>(total);
-        a.per_xcd = static_cast<int32_t>(per_xcd);
-        a.xcds = xcds;
-        a.grid_direct = static_cast<int32_t>(per_xcd * xcds);
-        a.split = static_cast<int32_t>(sp.split);
-        a.kv_per_split = static_cast<int32_t>(sp.kv_per_split);
-        const int64_t n_parts = sp.n_tail * sp.split;
-        if (sp.split > 0) {
-            a.ws_o = static_cast<float *>(p.ws);
-            a.ws_ml = a.ws_o + n_parts * kBr * p.head_dim;
-        }
-        a.scale_log2 = static_cast<float>(1.4426950408889634 / sqrt(static_cast<double>(p.head_dim)));
-        for (int i = 0; i < p.M; ++i) a.kf[i] = p.kf[i];
-        a.n_kv = p.n_kv;
-        a.tiles_per_frame = static_cast<int32_t>((p.N + kBc - 1) / kBc);
-        for (int i = 0; i < p.n_kv; ++i) a.kvf[i] = p.kvf[i];
-        if (p.cache_form) {
-            a.n_kv = walk;
-            for (int i = 0; i < walk; ++i) {
-                a.kvf[i] = p.cslot[i];
-                a.calpha[i] = p.calpha[i];
-            }
-            a.store = static_cast<const uint16_t *>(p.store);
-        }
-        if (a.n_kv > 0 && static_cast<int64_t>(a.n_kv) * a.tiles_per_frame > 0x7fffffffLL)
-            return hipErrorInvalidConfiguration;
-        const dim3 grid(static_cast<uint32_t>(per_xcd * xcds + n_parts)), block(kThreads);
-        if (p.cache_form) {
-            if (p.head_dim == 128) hipLaunchKernelGGL((attn_bf16_kernel<128, kFormCache>), grid, block, 0, stream, a);
-            else hipLaunchKernelGGL((attn_bf16_kernel<64, kFormCache>), grid, block, 0, stream, a);
-        } else if (p.n_kv > 0) {
-            if (p.head_dim == 128) hipLaunchKernelGGL((attn_bf16_kernel<128, kFormFrames>), grid, block, 0, stream, a);
-            else hipLaunchKernelGGL((attn_bf16_kernel<64, kFormFrames>), grid, block, 0, stream, a);
-        } else {
-            if (p.head_dim == 128) hipLaunchKernelGGL((attn_bf16_kernel<128, kFormDense>), grid, block, 0, stream, a);
-            else hipLaunchKernelGGL((attn_bf16_kernel<64, kFormDense>), grid, block, 0, stream, a);
-        }
-        if (sp.split == 0) return hipGetLastError();
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        CombineArgs c{};
-        c.ws_o = a.ws_o;
-        c.ws_ml = a.ws_ml;
-        c.out = a.out;
-        c.Mq = Mq;
-        c.heads = p.heads;
-        c.n_qtiles = a.n_qtiles;
-        c.first_tail = a.total_tiles;
-        c.split = a.split;
-        const int rows_per_wg = kCombineThreads / (p.head_dim / 8);
-        const dim3 cgrid(static_cast<uint32_t>(sp.n_tail * (kBr / rows_per_wg))), cblock(kCombineThreads);
-        if (p.head_dim == 128) hipLaunchKernelGGL(attn_combine_kernel<128>, cgrid, cblock, 0, stream, c);
-        else hipLaunchKernelGGL(attn_combine_kernel<64>, cgrid, cblock, 0, stream, c);
-        return hipGetLastError();
-    }
-    AttnF32Args a{};
-    a.q = static_cast<const float *>(p.q);
-    a.k = static_cast<const float *>(p.k);
-    a.v = static_cast<const float *>(p.v);
-    a.out = static_cast<float *>(p.out);
+    if (p.dtype == RF_F32) return launch_attention_f32(p, stream);
+    AttnKArgs a{};
+    a.q = static_cast<const uint16_t *>(p.q);
+    a.k = static_cast<const uint16_t *>(p.k);
+    a.v = static_cast<const uint16_t *>(p.v);
+    a.out = static_cast<uint16_t *>(p.out);
     a.S = p.S;
     a.N = p.N;
     a.Mq = Mq;
     a.heads = p.heads;
-    a.scale = static_cast<float>(1.0 / sqrt(static_cast<double>(p.head_dim)));
+    const int64_t nq = (Mq + kBr - 1) / kBr;
+    const int32_t xcds = p.geo.xcds;
+    if (p.geo.cus < 1 || xcds < 1 || xcds > 64) return hipErrorInvalidValue;
+    AttnSplit sp{};
+    sp.n_direct = nq * p.heads;
+    const int32_t walk = p.cache_form ? static_cast<int32_t>(p.S / p.N) : 0;
+    if (p.ws) {
+        sp = attention_split(Mq, p.heads, p.head_dim, p.N, p.S, p.n_kv, p.geo.cus, walk);
+        if (sp.split > 0 && p.ws_bytes < sp.ws_bytes) return hipErrorInvalidValue;
+    }
+    const int64_t total = sp.n_direct;
+    const int64_t per_xcd = (total + xcds - 1) / xcds;
+    if (nq * p.heads > 0x7fffffffLL / 64) return hipErrorInvalidConfiguration;
+    // per-lane load offsets inside a tile are 32-bit: a tile's token rows must span < 2 GiB
+    const int64_t kBc = key_tile(p.head_dim);
+    if (static_cast<int64_t>(p.heads) * p.head_dim * 2 * kBc >= 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    a.n_qtiles = static_cast<int32_t>(nq);
+    a.total_tiles = static_cast<int32_t>(total);
+    a.per_xcd = static_cast<int32_t>(per_xcd);
+    a.xcds = xcds;
+    a.grid_direct = static_cast<int32_t>(per_xcd * xcds);
+    a.split = static_cast<int32_t>(sp.split);
+    a.kv_per_split = static_cast<int32_t>(sp.kv_per_split);
+    const int64_t n_parts = sp.n_tail * sp.split;
+    if (sp.split > 0) {
+        a.ws_o = static_cast<float *>(p.ws);
+        a.ws_ml = a.ws_o + n_parts * kBr * p.head_dim;
+    }
+    a.scale_log2 = static_cast<float>(1.4426950408889634 / sqrt(static_cast<double>(p.head_dim)));
     for (int i = 0; i < p.M; ++i) a.kf[i] = p.kf[i];
     a.n_kv = p.n_kv;
+    a.tiles_per_frame = static_cast<int32_t>((p.N + kBc - 1) / kBc);
     for (int i = 0; i < p.n_kv; ++i) a.kvf[i] = p.kvf[i];
-    if (p.n_kv > 0) a.S = static_cast<int64_t>(p.n_kv) * p.N;
-    const int64_t nq = (Mq + kF32Rows - 1) / kF32Rows;
-    if (nq > 0x7fffffffLL || p.heads > 65535) return hipErrorInvalidConfiguration;
-    const dim3 grid(static_cast<uint32_t>(nq), static_cast<uint32_t>(p.heads)), block(2 * kF32Rows);
-    if (p.head_dim == 128) hipLaunchKernelGGL(attn_f32_kernel<128>, grid, block, 0, stream, a);
-    else hipLaunchKernelGGL(attn_f32_kernel<64>, grid, block, 0, stream, a);
+    if (p.cache_form) {
+        a.n_kv = walk;
+        for (int i = 0; i < walk; ++i) {
+            a.kvf[i] = p.cslot[i];
+            a.calpha[i] = p.calpha[i];
+        }
+        a.store = static_cast<const uint16_t *>(p.store);
+    }
+    if (a.n_kv > 0 && static_cast<int64_t>(a.n_kv) * a.tiles_per_frame > 0x7fffffffLL)
+        return hipErrorInvalidConfiguration;
+    const dim3 grid(static_cast<uint32_t>(per_xcd * xcds + n_parts)), block(kThreads);
+    if (p.cache_form) {
+        if (p.head_dim == 128) hipLaunchKernelGGL((attn_bf16_kernel<128, kFormCache>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((attn_bf16_kernel<64, kFormCache>), grid, block, 0, stream, a);
+    } else if (p.n_kv > 0) {
+        if (p.head_dim == 128) hipLaunchKernelGGL((attn_bf16_kernel<128, kFormFrames>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((attn_bf16_kernel<64, kFormFrames>), grid, block, 0, stream, a);
+    } else {
+        if (p.head_dim == 128) hipLaunchKernelGGL((attn_bf16_kernel<128, kFormDense>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((attn_bf16_kernel<64, kFormDense>), grid, block, 0, stream, a);
+    }
+    if (sp.split == 0) return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    CombineArgs c{};
+    c.ws_o = a.ws_o;
+    c.ws_ml = a.ws_ml;
+    c.out = a.out;
+    c.Mq = Mq;
+    c.heads = p.heads;
+    c.n_qtiles = a.n_qtiles;
+    c.first_tail = a.total_tiles;
+    c.split = a.split;
+    const int rows_per_wg = kCombineThreads / (p.head_dim / 8);
+    const dim3 cgrid(static_cast<uint32_t>(sp.n_tail * (kBr / rows_per_wg))), cblock(kCombineThreads);
+    if (p.head_dim == 128) hipLaunchKernelGGL(attn_combine_kernel<128>, cgrid, cblock, 0, stream, c);
+    else hipLaunchKernelGGL(attn_combine_kernel<64>, cgrid, cblock, 0, stream, c);
     return hipGetLastError();
 }
 

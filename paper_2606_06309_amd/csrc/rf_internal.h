@@ -47,7 +47,10 @@ struct AttnParams {
     // optional workspace for the split-key tail (NULL: no split)
     void *ws;
     int64_t ws_bytes;
-    // the device the launch runs on (bf16: the split plan and the XCD mapping)
+    // fp32: the keys of a query tile may be shared out among waves (calls whose
+    // rows need not match those of a launch of another size bit for bit)
+    int32_t split_keys;
+    // the device the launch runs on (the split plans and the XCD mapping)
     DeviceGeometry geo;
 };
 
@@ -68,8 +71,12 @@ struct AttnSplit {
 AttnSplit attention_split(int64_t Mq, int32_t heads, int32_t head_dim, int64_t N, int64_t S, int32_t n_kv,
                           int32_t cus, int32_t walk_frames = 0);
 
-
 hipError_t launch_attention(const AttnParams &p, hipStream_t stream);
+
+// The fp32 form (rf_attention_f32.hip), and whether it shares out the keys of
+// a launch of Mq query rows on `cus` compute units when split_keys allows it.
+hipError_t launch_attention_f32(const AttnParams &p, hipStream_t stream);
+bool f32_split_pays(int64_t Mq, int32_t heads, int32_t cus);
 
 // Static split-tail scratch of the allocation-free attention entry point (a
 // file-scope device array in rf_noalloc.hip): its size, and its device address
