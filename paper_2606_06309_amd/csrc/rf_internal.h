@@ -138,7 +138,6 @@ struct SimGeometry {
     int32_t L;                // feature elements per chunk
     int64_t chunks_per_plane;
     int64_t n_chunks;         // per batch element: C * chunks_per_plane
-    int64_t run;              // consecutive chunks one workgroup accumulates
     int64_t n_runs;           // workgroups (partial Gram blocks) per batch element
     int64_t workspace_bytes;  // B * n_runs * NBP * 16 doubles
 };

@@ -4,36 +4,40 @@
 // The frames of a batch element form a matrix X = [T][F] (F = C*H*W elements,
 // channel after channel); the similarity is the Gram matrix G = X X^T scaled
 // by the frame norms. F is large (10^5 .. 10^6) and T small (<= 256), so the
-// work is a bandwidth-bound reduction over F, split into chunks:
-//  1. gram_partial_kernel: a workgroup walks a run of consecutive feature
-//     chunks; for each it stages the chunk of all T frames in LDS (as
-//     [element][frame], frames padded to a multiple of 4) and accumulates 4x4
-//     frame blocks of the Gram matrix in double precision (fp32 x fp32
-//     products are exact in double). The run's partial blocks go to the
-//     workspace. fp32 latents of at most 64 frames whose planes are a
-//     multiple of 4 take gram_partial_dma_kernel instead: the chunk's frame
-//     rows stream from HBM into LDS through the load units, double-buffered.
-//     At most 512 workgroups in all (one round at two per compute unit),
-//     at least one per batch element, cover the batch.
+// work is a reduction over F, split over the workgroups of the device:
+//  1. gram_mfma_kernel (at most 64 frames): a wave walks chunks of 64 elements,
+//     loads all frames' elements of a chunk into registers (the next chunk's while
+//     this one is summed), widens them to fp64 once and accumulates every pair of
+//     4-frame blocks with v_mfma_f64_4x4x4_4b in fp64 (fp32 x fp32 products are
+//     exact there). The partial Gram blocks of a workgroup go to the workspace.
+//     What bounds it: for 33 frames 45 block pairs x 16 cycles per 16 elements of
+//     a SIMD (75 TFLOP/s of 78.6; 4x4 blocks lose 9 % of it to padding where 16x16
+//     ones would lose half, and run at 47), 4.4 us at 33 frames of 16 x 90 x 160,
+//     beside 30 MB of reads and the start and end of two launches. The vector form
+//     it replaces widened 32 operands for 64 fused multiply-adds. That shape:
+//     26.4 -> 17.8 us in all, fp32; bf16 32.3 -> 17.2.
+//     gram_wide_kernel (more frames) stages one chunk of all frames in LDS and
+//     sums 4x4 blocks with vector instructions.
 //  2. gram_reduce_kernel: a workgroup per 4x4 block pair sums the partials of
-//     all runs in a fixed order (deterministic) into the output matrix.
-//  3. cosine_normalize_kernel: one workgroup per batch element turns G into
+//     all runs in a fixed order (deterministic) into the cosines, or above 64
+//     frames into the Gram matrix, which
+//  3. cosine_normalize_kernel, one workgroup per batch element, turns into
 //     G_ij / (max(|x_i|, eps) * max(|x_j|, eps)) in place.
+#include <utility>
+
 #include "rf_internal.h"
 
 namespace rf {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kTileFloats = 16384;     // LDS floats for one staged chunk (64 KB)
-constexpr int kMaxChunk = 256;         // feature elements per chunk
+constexpr int kChunk = 64;             // feature elements a wave takes at a time (at most 64 frames)
+constexpr int kRunChunk = 256;         // elements the number of runs is counted in (at most 64 frames)
+constexpr int kTileFloats = 16384;     // LDS floats of one staged chunk (more than 64 frames; 64 KB)
+constexpr int kMaxWideChunk = 256;     // feature elements of one (more than 64 frames)
 constexpr double kNormFloor = 1e-8;
-#ifndef RF_SIM_TARGET_WORKGROUPS
-#define RF_SIM_TARGET_WORKGROUPS 512
-#endif
-constexpr int64_t kTargetWorkgroups = RF_SIM_TARGET_WORKGROUPS;   // partial-Gram workgroups per launch
-constexpr int kNarrowFrames = 64;            // padded frame count of the register-sum path
-static_assert(kNarrowFrames * kThreads <= kTileFloats, "narrow chunk must fit the LDS tile");
+constexpr int64_t kMaxWorkgroups = 512;      // partial-Gram workgroups per launch the workspace holds
+constexpr int kNarrowFrames = 64;            // padded frame count of the matrix-core path
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
@@ -42,14 +46,14 @@ struct PartialArgs {
     double *ws;
     int64_t plane;
     int64_t chunks_per_plane;
-    int64_t n_chunks;
-    int64_t run;              // chunks per workgroup
-    int64_t n_runs;           // workgroups per batch element
-    int32_t C, T, Tp, NB, NBP, L, KS;   // KS element slices per block pair (NBP < kThreads)
+    int64_t n_chunks;         // per batch element
+    int64_t n_runs;           // workgroups (partial Gram blocks) per batch element
+    int32_t C, T, Tp, NB, NBP, L;
 };
 
-__device__ inline float load_elem(const void *x, int64_t i, bool bf16) {
-    if (bf16) return __uint_as_float(static_cast<uint32_t>(static_cast<const uint16_t *>(x)[i]) << 16);
+template <bool kBf16>
+__device__ inline float load_elem(const void *x, int64_t i) {
+    if (kBf16) return __uint_as_float(static_cast<uint32_t>(static_cast<const uint16_t *>(x)[i]) << 16);
     return static_cast<const float *>(x)[i];
 }
 
@@ -64,40 +68,168 @@ __device__ inline void block_pair(int bp, int NB, int &bi, int &bj) {
     bj = row + rem;
 }
 
-// kWide = false (T <= 64): chunks of kThreads elements, at most kThreads block
-// pairs; each thread owns one block pair (or an element slice of one, KS > 1)
-// for the whole run of chunks and keeps its 16 sums in registers. kWide = true
-// (T > 64): shorter chunks, runs of one chunk; a thread walks several block
-// pairs and writes each one's sums when done.
-template <bool kBf16, bool kWide>
-__global__ __launch_bounds__(kThreads) void gram_partial_kernel(const PartialArgs a) {
+// ---- at most 64 frames: fp64 matrix cores ----
+
+// Four consecutive elements of one frame, as loaded: planes of any size put
+// them at any element's alignment.
+template <bool kBf16>
+struct Quad;
+template <>
+struct Quad<false> {
+    struct __attribute__((packed, aligned(4))) Raw { float v[4]; };
+    float v[4];
+    __device__ __forceinline__ void load(const void *x, int64_t i) {
+        const Raw r = *reinterpret_cast<const Raw *>(static_cast<const float *>(x) + i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = r.v[e];
+    }
+    __device__ __forceinline__ void load_part(const void *x, int64_t i, int n) {   // the first n of them
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = e < n ? load_elem<false>(x, i + e) : 0.0f;
+    }
+    __device__ __forceinline__ float get(int e) const { return v[e]; }
+};
+template <>
+struct Quad<true> {
+    struct __attribute__((packed, aligned(2))) Raw { uint32_t w[2]; };
+    uint32_t w[2];
+    __device__ __forceinline__ void load(const void *x, int64_t i) {
+        const Raw r = *reinterpret_cast<const Raw *>(static_cast<const uint16_t *>(x) + i);
+        w[0] = r.w[0];
+        w[1] = r.w[1];
+    }
+    __device__ __forceinline__ void load_part(const void *x, int64_t i, int n) {
+        const uint16_t *p = static_cast<const uint16_t *>(x) + i;
+        w[0] = (n > 0 ? p[0] : 0u) | (n > 1 ? static_cast<uint32_t>(p[1]) << 16 : 0u);
+        w[1] = (n > 2 ? p[2] : 0u) | (n > 3 ? static_cast<uint32_t>(p[3]) << 16 : 0u);
+    }
+    __device__ __forceinline__ float get(int e) const {
+        return __uint_as_float(e % 2 ? w[e / 2] & 0xffff0000u : w[e / 2] << 16);
+    }
+};
+
+// kNB = NB blocks of 4 frames. v_mfma_f64_4x4x4_4b multiplies four independent
+// 4x4 blocks over 4 elements each: lane l gives row l % 4 of both operands, so a
+// register that holds frame 4 b + l % 4 at element slot l / 4 is the A operand of
+// every pair (b, .) and the B operand of every pair (., b), and the four blocks
+// of an instruction are four quarters of the elements.
+template <int kNB, bool kBf16>
+__global__ __launch_bounds__(kThreads) void gram_mfma_kernel(const PartialArgs a) {
+    constexpr int kNBP = kNB * (kNB + 1) / 2;
+    constexpr int kGroup = 16;   // block pairs summed over the waves at a time
+    __shared__ double red[kGroup * kThreads];
+    const int64_t b = blockIdx.x / a.n_runs;
+    const int64_t rn = blockIdx.x - b * a.n_runs;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t waves = a.n_runs * (kThreads / 64);
+    const int64_t gw = rn * (kThreads / 64) + wave;
+    const int64_t c0 = gw * a.n_chunks / waves, c1 = (gw + 1) * a.n_chunks / waves;
+
+    // this lane's frame of each block (rows past the last frame repeat it: their
+    // entries are never written) and its elements inside a chunk
+    const int slot = 4 * (lane / 4);
+    const int64_t lane_off = (lane % 4) * a.plane + slot;
+    const int last = 4 * (kNB - 1) + lane % 4;
+    const int64_t last_off = (last < a.T ? last : a.T - 1) * a.plane + slot;
+    auto fetch = [&](int64_t chunk, Quad<kBf16> (&x)[kNB]) {
+        const int64_t c = chunk / a.chunks_per_plane;
+        const int64_t p0 = (chunk - c * a.chunks_per_plane) * kChunk;
+        const int64_t base = (b * a.C + c) * a.T * a.plane + p0;
+        if (p0 + kChunk <= a.plane) {
+#pragma unroll
+            for (int f = 0; f < kNB; ++f)
+                x[f].load(a.x, base + (f < kNB - 1 ? 4 * f * a.plane + lane_off : last_off));
+        } else {
+            const int64_t left = a.plane - p0 - slot;
+            const int n = static_cast<int>(left < 0 ? 0 : left < 4 ? left : 4);
+#pragma unroll
+            for (int f = 0; f < kNB; ++f)
+                x[f].load_part(a.x, base + (f < kNB - 1 ? 4 * f * a.plane + lane_off : last_off), n);
+        }
+    };
+    double acc[kNBP];
+#pragma unroll
+    for (int i = 0; i < kNBP; ++i) acc[i] = 0.0;
+    auto sum = [&](const Quad<kBf16> (&x)[kNB]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            double v[kNB];
+#pragma unroll
+            for (int f = 0; f < kNB; ++f) v[f] = static_cast<double>(x[f].get(e));
+            int i = 0;
+#pragma unroll
+            for (int bi = 0; bi < kNB; ++bi)
+#pragma unroll
+                for (int bj = bi; bj < kNB; ++bj, ++i)
+                    acc[i] = __builtin_amdgcn_mfma_f64_4x4x4f64(v[bi], v[bj], acc[i], 0, 0, 0);
+        }
+    };
+    Quad<kBf16> x0[kNB], x1[kNB];
+    if (c0 < c1) fetch(c0, x0);
+    for (int64_t chunk = c0; chunk < c1; chunk += 2) {
+        if (chunk + 1 < c1) fetch(chunk + 1, x1);
+        sum(x0);
+        if (chunk + 1 >= c1) break;
+        if (chunk + 2 < c1) fetch(chunk + 2, x0);
+        sum(x1);
+    }
+
+    // sum over the waves and the four blocks; lane 16 i + 4 q + j holds entry (i, j) of block q
+    double *dst = a.ws + (b * a.n_runs + rn) * kNBP * 16;
+#pragma unroll
+    for (int g = 0; g < kNBP; g += kGroup) {
+        constexpr int kAll = kNBP;
+        const int n = kAll - g < kGroup ? kAll - g : kGroup;
+        if (g > 0) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kGroup; ++i)
+            if (g + i < kAll) red[i * kThreads + tid] = acc[g + i < kAll ? g + i : 0];
+        __syncthreads();
+        if (tid < n * 16) {
+            const double *src = red + (tid / 16) * kThreads + (tid % 16) / 4 * 16 + tid % 4;
+            double s = 0.0;
+#pragma unroll
+            for (int w = 0; w < kThreads / 64; ++w)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) s += src[w * 64 + q * 4];
+            dst[g * 16 + tid] = s;
+        }
+    }
+}
+
+// ---- more than 64 frames ----
+
+// The chunk of all T frames is staged in LDS as [element][frame] (frames padded
+// with zeros to a multiple of 4); a thread walks several block pairs and writes
+// each one's 16 sums when done. A run is one chunk.
+template <bool kBf16>
+__global__ __launch_bounds__(kThreads) void gram_wide_kernel(const PartialArgs a) {
     extern __shared__ __attribute__((aligned(16))) float tile[];   // Tp * L floats (<= kTileFloats)
     const int64_t b = blockIdx.x / a.n_runs;
     const int64_t rn = blockIdx.x - b * a.n_runs;
     const int tid = threadIdx.x;
-    const int n_items = a.KS > 1 ? a.NBP * a.KS : a.NBP;
     double *dst = a.ws + (b * a.n_runs + rn) * a.NBP * 16;
-
-    auto stage = [&](int64_t chunk) {   // wide path: [element k][frame f], padding as 0
-        const int64_t c = chunk / a.chunks_per_plane;
-        const int64_t p0 = (chunk - c * a.chunks_per_plane) * a.L;
-        const int64_t frame0 = (b * a.C + c) * a.T;
-        for (int idx = tid; idx < a.Tp * a.L; idx += kThreads) {
-            const int f = idx / a.L, k = idx - f * a.L;
-            float v = 0.0f;
-            if (f < a.T && p0 + k < a.plane) v = load_elem(a.x, (frame0 + f) * a.plane + p0 + k, kBf16);
-            tile[k * a.Tp + f] = v;
-        }
-    };
-    // 16 sums of one 4x4 frame block pair over this chunk's elements k = ks, ks + KS, ...
-    auto accumulate = [&](int item, double (&acc)[16]) {
-        const int bp = a.KS > 1 ? item / a.KS : item;
-        const int ks = a.KS > 1 ? item - bp * a.KS : 0;
+    const int64_t c = rn / a.chunks_per_plane;
+    const int64_t p0 = (rn - c * a.chunks_per_plane) * a.L;
+    const int64_t frame0 = (b * a.C + c) * a.T;
+    for (int idx = tid; idx < a.Tp * a.L; idx += kThreads) {
+        const int f = idx / a.L, k = idx - f * a.L;
+        float v = 0.0f;
+        if (f < a.T && p0 + k < a.plane) v = load_elem<kBf16>(a.x, (frame0 + f) * a.plane + p0 + k);
+        tile[k * a.Tp + f] = v;
+    }
+    __syncthreads();
+    const f32x4_t *t4 = reinterpret_cast<const f32x4_t *>(tile);
+    const int row4 = a.Tp / 4;
+    for (int bp = tid; bp < a.NBP; bp += kThreads) {
         int bi, bj;
         block_pair(bp, a.NB, bi, bj);
-        const f32x4_t *t4 = reinterpret_cast<const f32x4_t *>(tile);
-        const int row4 = a.Tp / 4;
-        auto step = [&](int k) {
+        double acc[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = 0.0;
+#pragma unroll 4
+        for (int k = 0; k < a.L; ++k) {   // four elements' reads in flight
             const f32x4_t u = t4[k * row4 + bi];
             const f32x4_t w = t4[k * row4 + bj];
 #pragma unroll
@@ -105,212 +237,9 @@ __global__ __launch_bounds__(kThreads) void gram_partial_kernel(const PartialArg
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     acc[r * 4 + q] = fma(static_cast<double>(u[r]), static_cast<double>(w[q]), acc[r * 4 + q]);
-        };
-        int k = ks;
-        for (; k + 3 * a.KS < a.L; k += 4 * a.KS) {   // four elements' reads in flight
-            step(k);
-            step(k + a.KS);
-            step(k + 2 * a.KS);
-            step(k + 3 * a.KS);
         }
-        for (; k < a.L; k += a.KS) step(k);
-    };
-
-    if constexpr (kWide) {
-        stage(rn);   // a run is one chunk
-        __syncthreads();
-        for (int item = tid; item < n_items; item += kThreads) {
-            double acc[16];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[e] = 0.0;
-            accumulate(item, acc);
-#pragma unroll
-            for (int e = 0; e < 16; ++e) dst[item * 16 + e] = acc[e];
-        }
-    } else {
-        double acc[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[e] = 0.0;
-        const int64_t c0 = rn * a.run;
-        const int64_t c1 = (c0 + a.run < a.n_chunks) ? c0 + a.run : a.n_chunks;
-        for (int64_t chunk = c0; chunk < c1; ++chunk) {
-            const int64_t c = chunk / a.chunks_per_plane;
-            const int64_t p0 = (chunk - c * a.chunks_per_plane) * a.L;
-            const bool in = p0 + tid < a.plane;
-            const int64_t src = (b * a.C + c) * a.T * a.plane + (in ? p0 + tid : 0);
-            __syncthreads();   // the previous chunk is no longer read
-            // thread = element: its frames' values go out kBatch loads at a time
-            // (addresses clamped to a valid element, the values then masked) so
-            // the loads overlap instead of waiting one by one
-            constexpr int kBatch = 16;
-            for (int f0 = 0; f0 < a.Tp; f0 += kBatch) {
-                float v[kBatch];
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u) {
-                    const int f = f0 + u;
-                    const int fc = f < a.T ? f : a.T - 1;
-                    const float x = load_elem(a.x, src + static_cast<int64_t>(fc) * a.plane, kBf16);
-                    v[u] = (f < a.T && in) ? x : 0.0f;
-                }
-#pragma unroll
-                for (int u = 0; u < kBatch; ++u)
-                    if (f0 + u < a.Tp) tile[tid * a.Tp + f0 + u] = v[u];
-            }
-            __syncthreads();
-            if (tid < n_items) accumulate(tid, acc);
-        }
-        if (a.KS == 1) {
-            if (tid < n_items) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) dst[tid * 16 + e] = acc[e];
-            }
-        } else {
-            double *red = reinterpret_cast<double *>(tile);   // NBP * KS * 16 <= kThreads * 16 doubles
-            __syncthreads();
-            if (tid < n_items) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) red[tid * 16 + e] = acc[e];
-            }
-            __syncthreads();
-            for (int t = tid; t < a.NBP * 16; t += kThreads) {
-                const int bq = t / 16, e = t - bq * 16;
-                double sum = 0.0;
-                for (int j = 0; j < a.KS; ++j) sum += red[(bq * a.KS + j) * 16 + e];
-                dst[t] = sum;
-            }
-        }
-    }
-}
-
-// 16 bytes per lane from a buffer resource straight into LDS (lane l lands at
-// dst + 16 l); offsets at or past the resource's range read as zero.
-__device__ __forceinline__ void sim_load_lds16(__amdgpu_buffer_rsrc_t r, __attribute__((address_space(3))) void *dst,
-                                               int voffset) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, voffset, 0, 0, 0);
-}
-
-constexpr int kBufferWord3 = 0x00020000;   // raw buffer resource, gfx9-class GPUs
-
-// A pointer every lane holds the same value of, rebuilt from its first lane.
-__device__ __forceinline__ void *sim_uniform_ptr(const void *p) {
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(v >> 32));
-    return reinterpret_cast<void *>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
-// Narrow path for fp32 latents whose planes are a multiple of 4 elements: a
-// chunk's frame rows (256 elements = 1 KB each, [frame][element] order) go
-// from HBM straight into LDS, one wave-wide 16-byte-per-lane load per row,
-// double-buffered so the next chunk streams in while this one is summed;
-// elements past the plane read as zero through the load's range check, the
-// padding frames' rows are zeroed once. A thread accumulates its 4x4 block pair
-// over groups of 4 consecutive elements (8 LDS reads of 16 bytes per 64 fused
-// multiply-adds).
-__global__ __launch_bounds__(kThreads) void gram_partial_dma_kernel(const PartialArgs a) {
-    constexpr int kL = kThreads;
-    constexpr int kGroups = kL / 4;
-    extern __shared__ __attribute__((aligned(1024))) float tile[];   // 2 x [Tp][kL] floats
-    const int64_t b = blockIdx.x / a.n_runs;
-    const int64_t rn = blockIdx.x - b * a.n_runs;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n_items = a.KS > 1 ? a.NBP * a.KS : a.NBP;
-    double *dst = a.ws + (b * a.n_runs + rn) * a.NBP * 16;
-    const int buf_floats = a.Tp * kL;
-
-    // padding frames: zero rows in both buffers (never loaded)
-    for (int i = tid; i < 2 * (a.Tp - a.T) * kL; i += kThreads) {
-        const int bufi = i / ((a.Tp - a.T) * kL);
-        const int rem = i - bufi * (a.Tp - a.T) * kL;
-        tile[bufi * buf_floats + a.T * kL + rem] = 0.0f;
-    }
-
-    const int64_t c0 = rn * a.run;
-    const int64_t c1 = (c0 + a.run < a.n_chunks) ? c0 + a.run : a.n_chunks;
-    // loads of chunk `chunk` into buffer `bufi`: wave w takes frames w, w + 4, ...
-    auto issue = [&](int64_t chunk, int bufi) {
-        const int64_t c = chunk / a.chunks_per_plane;
-        const int64_t p0 = (chunk - c * a.chunks_per_plane) * kL;
-        const float *base = static_cast<const float *>(a.x) + ((b * a.C + c) * a.T) * a.plane + p0;
-        const int64_t left = (static_cast<int64_t>(a.T) * a.plane - p0) * 4;
-        const int32_t rec = __builtin_amdgcn_readfirstlane(
-            static_cast<int32_t>(left < 0x7fffffffLL ? left : 0x7fffffffLL));
-        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(sim_uniform_ptr(base), 0, rec,
-                                                                            kBufferWord3);
-        const bool in = p0 + 4 * lane < a.plane;
-        for (int f = wave; f < a.T; f += kThreads / 64) {
-            const int off = in ? static_cast<int>(f * a.plane * 4 + lane * 16) : static_cast<int>(0xfffffff0u);
-            sim_load_lds16(r, (__attribute__((address_space(3))) void *)(
-                                  reinterpret_cast<char *>(tile) + (bufi * buf_floats + f * kL) * 4),
-                           off);
-        }
-    };
-    auto done = [&]() {
-        __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's loads have reached LDS
-        __syncthreads();
-    };
-
-    double acc[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] = 0.0;
-    int bi = 0, bj = 0, ks = 0;
-    if (tid < n_items) {
-        const int bp = a.KS > 1 ? tid / a.KS : tid;
-        ks = a.KS > 1 ? tid - bp * a.KS : 0;
-        block_pair(bp, a.NB, bi, bj);
-    }
-    auto sum_chunk = [&](int bufi) {
-        if (tid >= n_items) return;
-        const f32x4_t *t4 = reinterpret_cast<const f32x4_t *>(tile + bufi * buf_floats);
-        for (int g = ks; g < kGroups; g += a.KS) {
-            f32x4_t u[4], w[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                u[r] = t4[(4 * bi + r) * kGroups + g];
-                w[r] = t4[(4 * bj + r) * kGroups + g];
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        acc[r * 4 + q] = fma(static_cast<double>(u[r][e]), static_cast<double>(w[q][e]),
-                                             acc[r * 4 + q]);
-        }
-    };
-    if (c0 < c1) issue(c0, 0);
-    done();
-    for (int64_t chunk = c0; chunk < c1; chunk += 2) {
-        if (chunk + 1 < c1) issue(chunk + 1, 1);
-        sum_chunk(0);
-        done();
-        if (chunk + 1 >= c1) break;
-        if (chunk + 2 < c1) issue(chunk + 2, 0);
-        sum_chunk(1);
-        done();
-    }
-    if (a.KS == 1) {
-        if (tid < n_items) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) dst[tid * 16 + e] = acc[e];
-        }
-    } else {
-        double *red = reinterpret_cast<double *>(tile);
-        __syncthreads();
-        if (tid < n_items) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) red[tid * 16 + e] = acc[e];
-        }
-        __syncthreads();
-        for (int t = tid; t < a.NBP * 16; t += kThreads) {
-            const int bq = t / 16, e = t - bq * 16;
-            double sum = 0.0;
-            for (int j = 0; j < a.KS; ++j) sum += red[(bq * a.KS + j) * 16 + e];
-            dst[t] = sum;
-        }
+        for (int e = 0; e < 16; ++e) dst[bp * 16 + e] = acc[e];
     }
 }
 
@@ -323,32 +252,67 @@ struct ReduceArgs {
 
 // One workgroup per (batch element, block pair): kReduceLanes lanes per Gram
 // entry sum the runs' partials with stride kReduceLanes, then the lane sums
-// are added in lane order.
+// are added in a tree. kCosine: the workgroup also sums the two diagonal blocks
+// of its frames, in the same order as their own workgroups do, and writes the
+// cosines, so no launch follows (the partials of at most 512 runs are read
+// three times instead of once: a few hundred KB from L2); otherwise the Gram
+// entries, for cosine_normalize_kernel.
 constexpr int kReduceThreads = 1024;
 constexpr int kReduceLanes = kReduceThreads / 16;
 
+template <bool kCosine>
 __global__ __launch_bounds__(kReduceThreads) void gram_reduce_kernel(const ReduceArgs a) {
-    __shared__ double lane_sum[kReduceThreads];
+    constexpr int kSums = kCosine ? 3 : 1;
+    __shared__ double part[kSums][kReduceThreads / 64][16];
+    __shared__ double total[kSums][16];
     const int64_t b = blockIdx.x / a.NBP;
     const int bp = static_cast<int>(blockIdx.x - b * a.NBP);
-    const int e = threadIdx.x % 16, lane = threadIdx.x / 16;
-    const double *src = a.ws + (b * a.n_runs * a.NBP + bp) * 16 + e;
-    double s = 0.0;
+    const int tid = threadIdx.x, e = tid % 16, lane = tid / 16;
+    int bi, bj;
+    block_pair(bp, a.NB, bi, bj);
+    // block pair (i, i) follows the i rows of NB, NB - 1, ... pairs before it
+    const int diag_i = bi * a.NB - bi * (bi - 1) / 2, diag_j = bj * a.NB - bj * (bj - 1) / 2;
+    const double *src = a.ws + b * a.n_runs * a.NBP * 16 + e;
+    const int64_t run = static_cast<int64_t>(a.NBP) * 16;
+    double s[kSums];
+#pragma unroll
+    for (int k = 0; k < kSums; ++k) s[k] = 0.0;
 #pragma unroll 4
-    for (int64_t r = lane; r < a.n_runs; r += kReduceLanes) s += src[r * a.NBP * 16];
-    lane_sum[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x < 16) {
-        double g = 0.0;
-        for (int l = 0; l < kReduceLanes; ++l) g += lane_sum[l * 16 + e];
-        int bi, bj;
-        block_pair(bp, a.NB, bi, bj);
-        const int i = 4 * bi + e / 4, j = 4 * bj + e % 4;
-        if (i < a.T && j < a.T) {
-            double *out = a.sim + b * a.T * a.T;
-            out[static_cast<int64_t>(i) * a.T + j] = g;
-            out[static_cast<int64_t>(j) * a.T + i] = g;   // same value twice on diagonal blocks
+    for (int64_t r = lane; r < a.n_runs; r += kReduceLanes) {
+        s[0] += src[r * run + bp * 16];
+        if constexpr (kCosine) {
+            s[1] += src[r * run + diag_i * 16];
+            s[2] += src[r * run + diag_j * 16];
         }
+    }
+#pragma unroll
+    for (int k = 0; k < kSums; ++k) {
+        s[k] += __shfl_xor(s[k], 16);
+        s[k] += __shfl_xor(s[k], 32);
+        if (tid % 64 < 16) part[k][tid / 64][e] = s[k];
+    }
+    __syncthreads();
+    if (tid < kSums * 16) {
+        double v[kReduceThreads / 64];
+#pragma unroll
+        for (int w = 0; w < kReduceThreads / 64; ++w) v[w] = part[lane][w][e];
+#pragma unroll
+        for (int n = kReduceThreads / 128; n > 0; n /= 2)
+#pragma unroll
+            for (int w = 0; w < n; ++w) v[w] += v[w + n];
+        total[lane][e] = v[0];
+    }
+    __syncthreads();
+    const int i = 4 * bi + e / 4, j = 4 * bj + e % 4;
+    if (tid < 16 && i <= j && j < a.T) {
+        double g = total[0][e];
+        if constexpr (kCosine) {
+            const double ni = sqrt(total[1][e / 4 * 5]), nj = sqrt(total[2][e % 4 * 5]);
+            g /= (ni > kNormFloor ? ni : kNormFloor) * (nj > kNormFloor ? nj : kNormFloor);
+        }
+        double *out = a.sim + b * a.T * a.T;
+        out[static_cast<int64_t>(i) * a.T + j] = g;
+        out[static_cast<int64_t>(j) * a.T + i] = g;
     }
 }
 
@@ -366,6 +330,19 @@ __global__ __launch_bounds__(kThreads) void cosine_normalize_kernel(double *sim,
     }
 }
 
+template <int kNB, bool kBf16>
+void launch_mfma(const PartialArgs &a, dim3 grid, hipStream_t stream) {
+    hipLaunchKernelGGL((gram_mfma_kernel<kNB, kBf16>), grid, dim3(kThreads), 0, stream, a);
+}
+
+// gram_mfma_kernel of 1..16 frame blocks
+template <bool kBf16, int... kNB>
+void launch_mfma_of(const PartialArgs &a, dim3 grid, hipStream_t stream, std::integer_sequence<int, kNB...>) {
+    static constexpr void (*const launch[])(const PartialArgs &, dim3, hipStream_t) = {
+        launch_mfma<kNB + 1, kBf16>...};
+    launch[a.NB - 1](a, grid, stream);
+}
+
 }  // namespace
 
 SimGeometry similarity_geometry(int32_t B, int32_t C, int32_t T, int64_t plane) {
@@ -373,19 +350,25 @@ SimGeometry similarity_geometry(int32_t B, int32_t C, int32_t T, int64_t plane) 
     g.Tp = (T + 3) / 4 * 4;
     g.NB = g.Tp / 4;
     g.NBP = g.NB * (g.NB + 1) / 2;
-    // T <= 64: chunks of exactly kThreads elements; larger T: as many as fit the tile
+    const bool wide = g.Tp > kNarrowFrames;
     const int L = (kTileFloats / g.Tp) / 16 * 16;
-    g.L = g.Tp <= kNarrowFrames ? kThreads : (L < kMaxChunk ? L : kMaxChunk);
+    g.L = !wide ? kChunk : L < kMaxWideChunk ? L : kMaxWideChunk;
     g.chunks_per_plane = (plane + g.L - 1) / g.L;
     g.n_chunks = static_cast<int64_t>(C) * g.chunks_per_plane;
-    // at most kTargetWorkgroups workgroups over the whole batch (one round at two
-    // per compute unit: a partly filled second round would double the time of
-    // the workgroups in it), at least one per batch element; each is a run of
-    // chunks (one chunk per run when a thread has to walk several block pairs)
-    const int64_t per_b = kTargetWorkgroups / B > 0 ? kTargetWorkgroups / B : 1;
-    g.run = g.Tp > kNarrowFrames ? 1 : (g.n_chunks + per_b - 1) / per_b;
-    g.n_runs = (g.n_chunks + g.run - 1) / g.run;
+    // The workspace holds at most kMaxWorkgroups runs over the whole batch and at
+    // least one per batch element; one per chunk above 64 frames.
+    const int64_t per_b = kMaxWorkgroups / B > 0 ? kMaxWorkgroups / B : 1;
+    const int64_t units = wide ? g.n_chunks : static_cast<int64_t>(C) * ((plane + kRunChunk - 1) / kRunChunk);
+    const int64_t run = wide ? 1 : (units + per_b - 1) / per_b;
+    g.n_runs = (units + run - 1) / run;
     g.workspace_bytes = static_cast<int64_t>(B) * g.n_runs * g.NBP * 16 * static_cast<int64_t>(sizeof(double));
+    // Up to 16 frames a chunk is bound by its loads and two workgroups per compute
+    // unit keep more of them in flight (5 videos of 13 frames of 61 x 105, 16
+    // channels: 11.9 us against 12.7 with one); with more, the matrix instructions
+    // of one wave fill a SIMD, and fewer partials are summed with one (33 frames of
+    // 90 x 160: 17.8 us against 18.8; 48 frames: 24.8 against 31.3).
+    const int64_t one_per_cu = kMaxWorkgroups / 2 / B > 0 ? kMaxWorkgroups / 2 / B : 1;
+    if (!wide && g.NB > 4 && g.n_runs > one_per_cu) g.n_runs = one_per_cu;
     return g;
 }
 
@@ -397,7 +380,6 @@ hipError_t launch_similarity(const SimParams &p, hipStream_t stream) {
     a.plane = p.plane;
     a.chunks_per_plane = g.chunks_per_plane;
     a.n_chunks = g.n_chunks;
-    a.run = g.run;
     a.n_runs = g.n_runs;
     a.C = p.C;
     a.T = p.T;
@@ -405,35 +387,18 @@ hipError_t launch_similarity(const SimParams &p, hipStream_t stream) {
     a.NB = g.NB;
     a.NBP = g.NBP;
     a.L = g.L;
-    a.KS = g.NBP >= kThreads ? 1 : kThreads / g.NBP;
     const int64_t blocks = static_cast<int64_t>(p.B) * g.n_runs;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const dim3 grid(static_cast<uint32_t>(blocks)), block(kThreads);
-    const bool wide = g.Tp > kNarrowFrames;
-    // the staged chunk, or the element-slice sums of the narrow path if larger
-    size_t lds = static_cast<size_t>(g.Tp) * g.L * sizeof(float);
-    const size_t red = static_cast<size_t>(kThreads) * 16 * sizeof(double);
-    if (!wide && a.KS > 1 && lds < red) lds = red;
-    // fp32, at most 64 frames, planes of a multiple of 4 elements and frame blocks
-    // addressable with 32-bit offsets: chunks streamed into LDS by the load units
-    const bool dma = p.dtype == RF_F32 && !wide && p.plane % 4 == 0 &&
-                     static_cast<int64_t>(p.T) * p.plane * 4 < 0x7ffff000LL;
-    if (dma) {
-        const size_t two = 2 * static_cast<size_t>(g.Tp) * g.L * sizeof(float);
-        const size_t bytes = two > lds ? two : lds;
-        if (bytes > 65536) {   // more than 64 KB of dynamic LDS must be allowed explicitly
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&gram_partial_dma_kernel),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     static_cast<int>(bytes));
-            if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL(gram_partial_dma_kernel, grid, block, bytes, stream, a);
-    } else if (p.dtype == RF_BF16) {
-        if (wide) hipLaunchKernelGGL((gram_partial_kernel<true, true>), grid, block, lds, stream, a);
-        else hipLaunchKernelGGL((gram_partial_kernel<true, false>), grid, block, lds, stream, a);
+    const bool wide = g.Tp > kNarrowFrames, bf16 = p.dtype == RF_BF16;
+    if (wide) {
+        const size_t lds = static_cast<size_t>(g.Tp) * g.L * sizeof(float);
+        if (bf16) hipLaunchKernelGGL(gram_wide_kernel<true>, grid, block, lds, stream, a);
+        else hipLaunchKernelGGL(gram_wide_kernel<false>, grid, block, lds, stream, a);
     } else {
-        if (wide) hipLaunchKernelGGL((gram_partial_kernel<false, true>), grid, block, lds, stream, a);
-        else hipLaunchKernelGGL((gram_partial_kernel<false, false>), grid, block, lds, stream, a);
+        constexpr std::make_integer_sequence<int, kNarrowFrames / 4> blocks_of_4{};
+        if (bf16) launch_mfma_of<true>(a, grid, stream, blocks_of_4);
+        else launch_mfma_of<false>(a, grid, stream, blocks_of_4);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -447,11 +412,15 @@ hipError_t launch_similarity(const SimParams &p, hipStream_t stream) {
     r.NBP = g.NBP;
     const int64_t rblocks = static_cast<int64_t>(p.B) * g.NBP;
     if (rblocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3(static_cast<uint32_t>(rblocks)), dim3(kReduceThreads), 0, stream, r);
+    const dim3 rgrid(static_cast<uint32_t>(rblocks)), rblock(kReduceThreads);
+    if (!wide) {
+        hipLaunchKernelGGL(gram_reduce_kernel<true>, rgrid, rblock, 0, stream, r);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(gram_reduce_kernel<false>, rgrid, rblock, 0, stream, r);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(cosine_normalize_kernel, dim3(static_cast<uint32_t>(p.B)), dim3(kThreads), 0, stream,
-                       p.sim, p.T);
+    hipLaunchKernelGGL(cosine_normalize_kernel, dim3(static_cast<uint32_t>(p.B)), block, 0, stream, p.sim, p.T);
     return hipGetLastError();
 }
 
