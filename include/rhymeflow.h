@@ -187,9 +187,10 @@ int rf_keyframe_attention(const void *q, const void *k, const void *v, void *out
  *   for the current device's compute units (compute_units = 0 there) (may be
  *   0: then nothing is split), not overlapping q, k, v or out; its
  *   contents are overwritten and meaningless afterwards. fp32 needs and
- *   touches none of it, but a small fp32 launch given one shares out the keys
- *   of each query tile among the waves of a workgroup (the same effect on
- *   the order of its sums).
+ *   touches none of it, but a small launch (of either type) given one shares
+ *   out the keys of each query tile among the waves of a workgroup instead of
+ *   splitting a tail (the same effect on the order of its sums) and leaves the
+ *   workspace alone.
  * Other arguments and errors as rf_keyframe_attention; RF_ERR_INVALID_ARG also
  * for a NULL or too small workspace or an overlap.
  */
@@ -252,8 +253,9 @@ typedef struct rf_attention_split {
 } rf_attention_split;
 
 /*
- * The split plan rf_keyframe_attention_ws / rf_frame_attention use for these
- * sizes on compute_units compute units (arguments and errors as
+ * The split plan rf_keyframe_attention_ws / rf_frame_attention have for these
+ * sizes (a small launch needs its workspace but may run without the split)
+ * on compute_units compute units (arguments and errors as
  * rf_attention_workspace). For RF_F32 every count is 0 (no split).
  */
 int rf_attention_plan(int32_t M, int32_t Mkv, int32_t T, int32_t H, int32_t W, int32_t heads, int32_t head_dim,

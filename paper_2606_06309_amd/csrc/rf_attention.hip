@@ -43,6 +43,9 @@
 //    are then split along the keys into parts that run as extra workgroups;
 //    each part writes its unnormalised (O, m, l) in fp32, and a small kernel
 //    combines the parts of a tile (max of the references, rescaled sums).
+//  * Small launches (when the caller provides a workspace or names the static
+//    scratch): attn_bf16_small_kernel, 32 rows a workgroup, the keys shared out
+//    among its waves; the rule is at small_pays.
 //  * Frame-level key/value mask (the frame-list form): the key loop walks a list
 //    of frames in key tiles that never cross a frame; masked frames are
 //    never read.
@@ -274,6 +277,36 @@ __device__ __forceinline__ void pv_tile(const uint8_t *vb, const int (&vofs)[D /
     __builtin_amdgcn_sched_group_barrier(0x008, kLead, 0);
 }
 
+// Query fragments: B operand of S^T = K Q^T (fused keyframe gather).
+template <int D>
+__device__ __forceinline__ void load_queries(const AttnKArgs &a, int64_t row, int head, int grp,
+                                             u32x4_t (&qf)[D / 16]) {
+    if (row < a.Mq) {
+        const int64_t f = row / a.N;
+        const int64_t tok = static_cast<int64_t>(a.kf[f]) * a.N + (row - f * a.N);
+        const uint16_t *qp = a.q + (tok * a.heads + head) * D + grp * 8;
+#pragma unroll
+        for (int kk = 0; kk < D / 16; ++kk) qf[kk] = *reinterpret_cast<const u32x4_t *>(qp + kk * 16);
+    } else {
+#pragma unroll
+        for (int kk = 0; kk < D / 16; ++kk) qf[kk] = u32x4_t{0u, 0u, 0u, 0u};
+    }
+}
+
+// LDS byte offsets of a lane's K fragment (block 0, step kk) and of its V^T operand halves.
+template <int D>
+__device__ __forceinline__ void fragment_offsets(int lane, int (&kofs)[D / 16], int (&vofs)[D / 32]) {
+    using L = TileLayout<D>;
+    const int col = lane & 31, grp = lane >> 5;
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) kofs[kk] = col * L::kRow + (((2 * kk) ^ grp ^ L::kswz(col)) * 16);
+    const int g16 = (lane >> 4) & 1, j = lane & 15;
+    const int rr = grp * 4 + j / 4;   // key row within each 8-key half of a 16-key group
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+        vofs[db] = rr * L::kRow + (((2 * db + g16) ^ (L::vswz(rr) / 2)) * 32) + 8 * (j % 4);
+}
+
 // Per-tile pipeline, double-buffered LDS, one barrier per tile:
 //   issue the global->LDS loads of tile t+1 into the buffer tile t-1 used
 //   math on tile t
@@ -319,19 +352,9 @@ void attn_bf16_kernel(const AttnKArgs a) {
     const int col = lane & 31, grp = lane >> 5;
     const int64_t rs = static_cast<int64_t>(a.heads) * D;   // token stride in elements
 
-    // ---- query fragments: B operand of S^T = K Q^T (fused keyframe gather) ----
     const int64_t row = static_cast<int64_t>(qt) * kBr + wave * 32 + col;
     u32x4_t qf[D / 16];
-    if (row < a.Mq) {
-        const int64_t f = row / a.N;
-        const int64_t tok = static_cast<int64_t>(a.kf[f]) * a.N + (row - f * a.N);
-        const uint16_t *qp = a.q + tok * rs + static_cast<int64_t>(head) * D + grp * 8;
-#pragma unroll
-        for (int kk = 0; kk < D / 16; ++kk) qf[kk] = *reinterpret_cast<const u32x4_t *>(qp + kk * 16);
-    } else {
-#pragma unroll
-        for (int kk = 0; kk < D / 16; ++kk) qf[kk] = u32x4_t{0u, 0u, 0u, 0u};
-    }
+    load_queries<D>(a, row, head, grp, qf);
 
     // ---- per-lane offsets, fixed for the whole loop ----
     // global byte offsets (from the tile's first key) of this lane's 16 bytes in each load
@@ -343,17 +366,8 @@ void attn_bf16_kernel(const AttnKArgs a) {
         kgo[i] = static_cast<int>(key * rs * 2) + (slot ^ L::kswz(key)) * 16;
         vgo[i] = static_cast<int>(key * rs * 2) + (slot ^ L::vswz(key)) * 16;
     }
-    // LDS byte offsets of the K fragment (block 0, step kk) and of the V^T operand halves
     int kofs[D / 16], vofs[D / 32];
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) kofs[kk] = col * L::kRow + (((2 * kk) ^ grp ^ L::kswz(col)) * 16);
-    {
-        const int g16 = (lane >> 4) & 1, j = lane & 15;
-        const int rr = grp * 4 + j / 4;   // key row within each 8-key half of a 16-key group
-#pragma unroll
-        for (int db = 0; db < D / 32; ++db)
-            vofs[db] = rr * L::kRow + (((2 * db + g16) ^ (L::vswz(rr) / 2)) * 32) + 8 * (j % 4);
-    }
+    fragment_offsets<D>(lane, kofs, vofs);
 
     f32x16_t oacc[D / 32];
 #pragma unroll
@@ -637,6 +651,214 @@ void attn_bf16_kernel(const AttnKArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// Small launches: a workgroup owns 32 query rows of one head and its 8 waves
+// share out the keys, wave w taking tiles w, w + 8, ...; the parts are merged
+// through LDS at the end. Each wave streams its tiles into LDS of its own (one K
+// and one V buffer: the next K is fetched while this tile's softmax and second
+// product run, the next V under the next tile's scores), so the loop has no
+// barrier and no second kernel follows.
+// What bounds it: a CU reads K and V once per 32 rows instead of once per 256,
+// 32 FLOP per byte through its L1, which is half of what the matrix cores could
+// take; a launch that leaves most CUs idle in 256-row tiles has that to spare.
+// Kernel and combine against this one: 9 frames of 17 x 31, 5 heads x 64, three
+// keyframes 31.1 -> 19.0 us (504 TFLOP/s); 13 of 16 x 16, 8 x 64, four 27.1 ->
+// 15.6; 9 of 10 x 13, 3 x 128, three 24.5 -> 11.5.
+// ---------------------------------------------------------------------------
+
+constexpr int kSmallRows = 32;
+// 8 KB of K and of V a tile at either head dimension: 128 KB of LDS
+__host__ __device__ constexpr int small_key_tile(int head_dim) { return head_dim == 64 ? 64 : 32; }
+
+// The softmax of attn_bf16_kernel's tiles, step for step (there it stays inside
+// the kernel: called as this function, the compiler's schedule of its head
+// dimension 64 form loses 4 %, 1001 against 1040 TFLOP/s).
+template <int D, int kNB>
+__device__ __forceinline__ void softmax_tile(f32x16_t (&sacc)[kNB], int32_t valid, int grp, float sl2, float &m_run,
+                                             float &l_run, f32x16_t (&oacc)[D / 32], u32x4_t (&pw)[2 * kNB]) {
+    if (valid < 32 * kNB) {
+#pragma unroll
+        for (int b = 0; b < kNB; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (b * 32 + (r / 4) * 8 + grp * 4 + r % 4 >= valid) sacc[b][r] = -__builtin_huge_valf();
+    }
+    auto probs = [&]() {
+        float lsp[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int b = 0; b < kNB; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) {
+                const float p0 = fast_exp2(fmaf(sacc[b][r], sl2, -m_run));
+                const float p1 = fast_exp2(fmaf(sacc[b][r + 1], sl2, -m_run));
+                const uint32_t word = pack_bf16x2(p0, p1);
+                lsp[(r / 2) % 4] = add_bf16x2(word, lsp[(r / 2) % 4]);
+                pw[b * 2 + r / 8][(r % 8) / 2] = word;
+            }
+        return ((lsp[0] + lsp[1]) + lsp[2]) + lsp[3];
+    };
+    float ls = probs();
+    if (!(halves_sum(ls) <= kRebaseBound)) {
+        float mx = -__builtin_huge_valf();
+#pragma unroll
+        for (int b = 0; b < kNB; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[b][r]);
+        const float m_new = fmaxf(m_run, halves_max(mx) * sl2);
+        const float corr = fast_exp2(m_run - m_new);
+        m_run = m_new;
+        l_run *= corr;
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[db][r] *= corr;
+        ls = probs();
+    }
+    l_run += ls;
+}
+
+template <int D, bool kFrames>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
+void attn_bf16_small_kernel(const AttnKArgs a) {
+    using L = TileLayout<D>;
+    constexpr int kBc = small_key_tile(D);
+    constexpr int kNB = kBc / 32;
+    constexpr int kTileBytes = kBc * L::kRow;
+    constexpr int kLoads = kTileBytes / 1024;
+    __shared__ __attribute__((aligned(1024))) uint8_t ks[kWaves * kTileBytes];
+    __shared__ __attribute__((aligned(1024))) uint8_t vs[kWaves * kTileBytes];
+    __shared__ float ml[kWaves][kSmallRows][2];
+
+    const int bid = blockIdx.x;
+    const int tile = (bid % a.xcds) * a.per_xcd + bid / a.xcds;
+    if (tile >= a.total_tiles) return;
+    const int head = tile / a.n_qtiles;
+    const int qt = tile - head * a.n_qtiles;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, grp = lane >> 5;
+    const int64_t rs = static_cast<int64_t>(a.heads) * D;
+    uint8_t *kb = ks + wave * kTileBytes;
+    uint8_t *vb = vs + wave * kTileBytes;
+
+    u32x4_t qf[D / 16];
+    load_queries<D>(a, static_cast<int64_t>(qt) * kSmallRows + col, head, grp, qf);
+    int kofs[D / 16], vofs[D / 32];
+    fragment_offsets<D>(lane, kofs, vofs);
+    int kgo[kLoads], vgo[kLoads];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+        const int key = i * L::kRowsPerLoad + lane / L::kSlots;
+        const int slot = lane % L::kSlots;
+        kgo[i] = static_cast<int>(key * rs * 2) + (slot ^ L::kswz(key)) * 16;
+        vgo[i] = static_cast<int>(key * rs * 2) + (slot ^ L::vswz(key)) * 16;
+    }
+    f32x16_t oacc[D / 32];
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[db][r] = 0.0f;
+    float m_run = -__builtin_huge_valf(), l_run = 0.0f;
+
+    struct Geom {
+        int64_t tok0;
+        int32_t valid;
+    };
+    auto geom = [&](int64_t t) {
+        Geom g;
+        int64_t left;
+        if constexpr (kFrames) {
+            const int32_t m = static_cast<int32_t>(t) / a.tiles_per_frame;
+            const int64_t o = (t - static_cast<int64_t>(m) * a.tiles_per_frame) * kBc;
+            g.tok0 = static_cast<int64_t>(a.kvf[m]) * a.N + o;
+            left = a.N - o;
+        } else {
+            g.tok0 = t * kBc;
+            left = a.S - g.tok0;
+        }
+        g.valid = static_cast<int32_t>(left < kBc ? left : kBc);
+        return g;
+    };
+    // the resource starts at the tile's first key and ends at its last valid one
+    auto issue = [&](const Geom &g, const uint16_t *tensor, const int (&go)[kLoads], uint8_t *dst) {
+        const int32_t rec = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(((g.valid - 1) * rs + D) * 2));
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            uniform_ptr(tensor + g.tok0 * rs + static_cast<int64_t>(head) * D), 0, rec, kBufferWord3);
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) load_lds16(r, (lds_void_t *)(dst + i * 1024), go[i]);
+    };
+
+    const int64_t n = kFrames ? static_cast<int64_t>(a.n_kv) * a.tiles_per_frame : (a.S + kBc - 1) / kBc;
+    if (wave < n) {
+        Geom g = geom(wave);
+        issue(g, a.k, kgo, kb);
+        issue(g, a.v, vgo, vb);
+        for (int64_t t = wave; t < n; t += kWaves) {
+            // (past the last tile it is fetched again and not used: with the loads on every
+            // path the waits below can be counted instead of draining both tensors)
+            const Geom nxt = geom(t + kWaves < n ? t + kWaves : t);
+            wait_loads<kLoads>();   // K is there; V may still be in flight
+            f32x16_t sacc[kNB];
+            scores_tile<D, kNB>(kb, kofs, qf, sacc);
+            wait_lds_reads();       // K is read: its buffer is free
+            issue(nxt, a.k, kgo, kb);
+            u32x4_t pw[2 * kNB];
+            softmax_tile<D, kNB>(sacc, g.valid, grp, a.scale_log2, m_run, l_run, oacc, pw);
+            wait_loads<kLoads>();   // V is there; the next K may still be in flight
+            pv_tile<D, kNB>(vb, vofs, pw, oacc);
+            wait_lds_reads();
+            issue(nxt, a.v, vgo, vb);
+            g = nxt;
+        }
+        wait_loads<0>();   // nothing lands in the buffers any more
+    }
+
+    // ---- merge: dimensions 0..63 of a wave's O rows go into its own K buffer, 64..127
+    // into its V buffer, 256 bytes a row, their 16-byte units permuted by row % 16 ----
+    const float l = halves_sum(l_run);
+    if (grp == 0) {
+        ml[wave][col][0] = m_run;
+        ml[wave][col][1] = l;
+    }
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+            const int unit = ((db % 2) * 8 + g4 * 2 + grp) ^ (col & 15);
+            *reinterpret_cast<f32x4_t *>((db < 2 ? kb : vb) + col * 256 + unit * 16) =
+                f32x4_t{oacc[db][g4 * 4], oacc[db][g4 * 4 + 1], oacc[db][g4 * 4 + 2], oacc[db][g4 * 4 + 3]};
+        }
+    __syncthreads();
+    const int r = tid / 16, unit = tid % 16;   // 512 threads: 32 rows x 16 units
+    const int64_t row = static_cast<int64_t>(qt) * kSmallRows + r;
+    if (row >= a.Mq) return;
+    float m = ml[0][r][0];
+#pragma unroll
+    for (int p = 1; p < kWaves; ++p) m = fmaxf(m, ml[p][r][0]);
+    float wgt[kWaves], lsum = 0.0f;
+#pragma unroll
+    for (int p = 0; p < kWaves; ++p) {
+        wgt[p] = fast_exp2(ml[p][r][0] - m);
+        lsum = fmaf(wgt[p], ml[p][r][1], lsum);
+    }
+    const float inv = 1.0f / lsum;
+    uint16_t *op = a.out + row * rs + static_cast<int64_t>(head) * D + unit * 4;
+#pragma unroll
+    for (int half = 0; half < D / 64; ++half) {
+        f32x4_t x = {};
+#pragma unroll
+        for (int p = 0; p < kWaves; ++p) {
+            const f32x4_t y = *reinterpret_cast<const f32x4_t *>((half == 0 ? ks : vs) + p * kTileBytes + r * 256 +
+                                                                 (unit ^ (r & 15)) * 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = fmaf(wgt[p], y[e], x[e]);
+        }
+        const u32x2_t w = {pack_bf16x2(x[0] * inv, x[1] * inv), pack_bf16x2(x[2] * inv, x[3] * inv)};
+        *reinterpret_cast<u32x2_t *>(op + half * 64) = w;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Combine of the split tail: for each row of a tail tile, the parts' reference
 // maxima m_p (log2 domain), row sums l_p and unnormalised outputs O_p give
 //   m = max_p m_p,  out = sum_p 2^(m_p - m) O_p / sum_p 2^(m_p - m) l_p,
@@ -752,6 +974,26 @@ AttnSplit attention_split(int64_t Mq, int32_t heads, int32_t head_dim, int64_t N
     return sp;
 }
 
+// Whether the small kernel ends earlier than whole tiles and a split tail.
+// Both are counted in keys walked by a CU's eight waves over 256 rows, 16.3 ns a
+// key at head dimension 64 and 27 at 128: whole rounds of all keys, the tail's
+// share of a round and, for the parts' results and their combine, about 400 keys;
+// against rounds of 32-row workgroups, each at 2.6 ns a key (0.16) or 5.3 (0.195;
+// 0.125 would be an eighth). Measured, split against small kernel: 21 frames of
+// 16 x 16, 12 x 64, five keyframes (60 tiles in quarters; 480 small ones)
+// 34.5 us against 36.9; 9 of 17 x 31, 5 x 128, three (35 in sevenths; 250) 37.3
+// against 32.7; 13 of 16 x 16, 12 x 128, four (48 in fifths; 384) 36.8 against 43.9.
+bool small_pays(const AttnSplit &sp, int64_t Mq, int32_t heads, int32_t head_dim, int64_t kv_tiles, int32_t cus) {
+    const int64_t bc = small_key_tile(head_dim), keys = kv_tiles * bc;
+    const int64_t rounds = (sp.n_direct + cus - 1) / cus;
+    const double tail = sp.split > 0 ? static_cast<double>((sp.n_tail * sp.split + cus - 1) / cus) / sp.split : 0.0;
+    const double whole = (rounds + tail) * keys + (sp.split > 0 ? 400.0 : 0.0);
+    const int64_t small_tiles = (Mq + kSmallRows - 1) / kSmallRows * heads;
+    const int64_t small_rounds = (small_tiles + cus - 1) / cus;
+    const int64_t small_keys = (kv_tiles + kWaves - 1) / kWaves * kWaves * bc;   // the wave with most tiles
+    return small_rounds * small_keys * (head_dim == 64 ? 0.16 : 0.195) < 0.95 * whole;
+}
+
 hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {
     const int64_t Mq = static_cast<int64_t>(p.M) * p.N;
     if (p.dtype == RF_F32) return launch_attention_f32(p, stream);
@@ -774,13 +1016,20 @@ hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {
         sp = attention_split(Mq, p.heads, p.head_dim, p.N, p.S, p.n_kv, p.geo.cus, walk);
         if (sp.split > 0 && p.ws_bytes < sp.ws_bytes) return hipErrorInvalidValue;
     }
+    const int64_t bc_small = small_key_tile(p.head_dim);
+    const int64_t kv_small = p.n_kv > 0 ? p.n_kv * ((p.N + bc_small - 1) / bc_small) : (p.S + bc_small - 1) / bc_small;
+    const bool small = p.split_keys && !p.cache_form && small_pays(sp, Mq, p.heads, p.head_dim, kv_small, p.geo.cus);
+    if (small) {
+        sp = AttnSplit{};
+        sp.n_direct = (Mq + kSmallRows - 1) / kSmallRows * p.heads;
+    }
     const int64_t total = sp.n_direct;
     const int64_t per_xcd = (total + xcds - 1) / xcds;
     if (nq * p.heads > 0x7fffffffLL / 64) return hipErrorInvalidConfiguration;
     // per-lane load offsets inside a tile are 32-bit: a tile's token rows must span < 2 GiB
-    const int64_t kBc = key_tile(p.head_dim);
+    const int64_t kBc = small ? small_key_tile(p.head_dim) : key_tile(p.head_dim);
     if (static_cast<int64_t>(p.heads) * p.head_dim * 2 * kBc >= 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    a.n_qtiles = static_cast<int32_t>(nq);
+    a.n_qtiles = static_cast<int32_t>(small ? (Mq + kSmallRows - 1) / kSmallRows : nq);
     a.total_tiles = static_cast<int32_t>(total);
     a.per_xcd = static_cast<int32_t>(per_xcd);
     a.xcds = xcds;
@@ -808,7 +1057,13 @@ hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {
     if (a.n_kv > 0 && static_cast<int64_t>(a.n_kv) * a.tiles_per_frame > 0x7fffffffLL)
         return hipErrorInvalidConfiguration;
     const dim3 grid(static_cast<uint32_t>(per_xcd * xcds + n_parts)), block(kThreads);
-    if (p.cache_form) {
+    if (small) {
+        const bool frames = p.n_kv > 0;
+        if (p.head_dim == 128 && frames) hipLaunchKernelGGL((attn_bf16_small_kernel<128, true>), grid, block, 0, stream, a);
+        else if (p.head_dim == 128) hipLaunchKernelGGL((attn_bf16_small_kernel<128, false>), grid, block, 0, stream, a);
+        else if (frames) hipLaunchKernelGGL((attn_bf16_small_kernel<64, true>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((attn_bf16_small_kernel<64, false>), grid, block, 0, stream, a);
+    } else if (p.cache_form) {
         if (p.head_dim == 128) hipLaunchKernelGGL((attn_bf16_kernel<128, kFormCache>), grid, block, 0, stream, a);
         else hipLaunchKernelGGL((attn_bf16_kernel<64, kFormCache>), grid, block, 0, stream, a);
     } else if (p.n_kv > 0) {

@@ -216,20 +216,6 @@ __device__ __forceinline__ void f32_pv(F32Wave<D> &w, const uint8_t *vb, const f
     }
 }
 
-// At most kLoads of this wave's memory loads still in flight (vmcnt is six bits, split).
-template <int kLoads>
-__device__ __forceinline__ void wait_loads() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0x0f70 | (kLoads & 15) | ((kLoads >> 4) << 14));
-    asm volatile("" ::: "memory");
-}
-// Every LDS read of this wave has returned.
-__device__ __forceinline__ void wait_lds_reads() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    asm volatile("" ::: "memory");
-}
-
 template <int D>
 __device__ __forceinline__ int64_t key_tiles(const AttnF32Args &a, int keys) {
     return a.n_kv > 0 ? static_cast<int64_t>(a.n_kv) * a.tiles_per_frame : (a.S + keys - 1) / keys;

@@ -39,4 +39,18 @@ __device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, lds_void_t 
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, voffset, 0, 0, 0);
 }
 
+// At most kLoads of this wave's memory loads still in flight (vmcnt is six bits, split).
+template <int kLoads>
+__device__ __forceinline__ void wait_loads() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0f70 | (kLoads & 15) | ((kLoads >> 4) << 14));
+    asm volatile("" ::: "memory");
+}
+// Every LDS read of this wave has returned.
+__device__ __forceinline__ void wait_lds_reads() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    asm volatile("" ::: "memory");
+}
+
 }  // namespace rf

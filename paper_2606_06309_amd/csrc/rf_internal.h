@@ -47,8 +47,8 @@ struct AttnParams {
     // optional workspace for the split-key tail (NULL: no split)
     void *ws;
     int64_t ws_bytes;
-    // fp32: the keys of a query tile may be shared out among waves (calls whose
-    // rows need not match those of a launch of another size bit for bit)
+    // the keys of a query tile may be shared out among waves (calls whose rows
+    // need not match those of a launch of another size bit for bit)
     int32_t split_keys;
     // the device the launch runs on (the split plans and the XCD mapping)
     DeviceGeometry geo;
