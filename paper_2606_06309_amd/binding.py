@@ -110,6 +110,9 @@ _vp = ctypes.c_void_p
 _i32p = ctypes.POINTER(ctypes.c_int32)
 _u8p = ctypes.POINTER(ctypes.c_uint8)
 _dp = ctypes.POINTER(ctypes.c_double)
+_double3 = ctypes.c_double * 3
+_I32 = np.dtype(np.int32)
+_U8 = np.dtype(np.uint8)
 
 lib.rf_status_string.argtypes = [ctypes.c_int]
 lib.rf_status_string.restype = ctypes.c_char_p
@@ -117,23 +120,23 @@ lib.rf_last_error.argtypes = []
 lib.rf_last_error.restype = ctypes.c_char_p
 lib.rf_abi_version.argtypes = []
 lib.rf_abi_version.restype = ctypes.c_int
-lib.rf_select_keyframes.argtypes = [_i32p, _i32, _i32, ctypes.c_uint32, _i32p, _i32p, _u8p]
+lib.rf_select_keyframes.argtypes = [_vp, _i32, _i32, ctypes.c_uint32, _i32p, _i32p, _u8p]
 lib.rf_select_keyframes.restype = ctypes.c_int
 lib.rf_keyframes_stride.argtypes = [_i32, _i32, _i32p, _i32p]
 lib.rf_keyframes_stride.restype = ctypes.c_int
 lib.rf_keyframes_uniform.argtypes = [_i32, _i32, _i32p, _i32p]
 lib.rf_keyframes_uniform.restype = ctypes.c_int
-lib.rf_project_latents.argtypes = [_vp, _vp, _dp, _u8p, _i32, _i32, _i32, _i32, _i32, _i32, _vp]
+lib.rf_project_latents.argtypes = [_vp, _vp, _dp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _vp]
 lib.rf_project_latents.restype = ctypes.c_int
-lib.rf_keyframe_attention.argtypes = [_vp, _vp, _vp, _vp, _i32p, _i32, _i32, _i32, _i32,
+lib.rf_keyframe_attention.argtypes = [_vp, _vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32,
                                       _i32, _i32, _i32, _vp]
 lib.rf_keyframe_attention.restype = ctypes.c_int
-lib.rf_frame_attention.argtypes = [_vp, _vp, _vp, _vp, _i32p, _i32, _i32p, _i32, _i32, _i32, _i32,
+lib.rf_frame_attention.argtypes = [_vp, _vp, _vp, _vp, _vp, _i32, _vp, _i32, _i32, _i32, _i32,
                                    _i32, _i32, _i32, _vp, _i64, _vp]
-lib.rf_keyframe_attention_ws.argtypes = [_vp, _vp, _vp, _vp, _i32p, _i32, _i32, _i32, _i32,
+lib.rf_keyframe_attention_ws.argtypes = [_vp, _vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32,
                                          _i32, _i32, _i32, _vp, _i64, _vp]
 lib.rf_keyframe_attention_ws.restype = ctypes.c_int
-lib.rf_keyframe_attention_noalloc.argtypes = [_vp, _vp, _vp, _vp, _i32p, _i32, _i32, _i32, _i32,
+lib.rf_keyframe_attention_noalloc.argtypes = [_vp, _vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32,
                                               _i32, _i32, _i32, _vp]
 lib.rf_keyframe_attention_noalloc.restype = ctypes.c_int
 RF_NOALLOC_SCRATCH_BYTES = 160 << 20
@@ -143,9 +146,9 @@ lib.rf_attention_plan.argtypes = [_i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32
                                   ctypes.POINTER(rf_attention_split)]
 lib.rf_attention_plan.restype = ctypes.c_int
 lib.rf_frame_attention.restype = ctypes.c_int
-lib.rf_gather_frames.argtypes = [_vp, _vp, _i32p, _i32, _i32, _i64, _i64, _vp]
+lib.rf_gather_frames.argtypes = [_vp, _vp, _vp, _i32, _i32, _i64, _i64, _vp]
 lib.rf_gather_frames.restype = ctypes.c_int
-lib.rf_scatter_frames.argtypes = [_vp, _vp, _i32p, _i32, _i32, _i64, _i64, _vp]
+lib.rf_scatter_frames.argtypes = [_vp, _vp, _vp, _i32, _i32, _i64, _i64, _vp]
 lib.rf_scatter_frames.restype = ctypes.c_int
 lib.rf_frame_similarity.argtypes = [_vp, _vp, _vp, _i64, _i32, _i32, _i32, _i32, _i32, _i32, _vp]
 lib.rf_frame_similarity.restype = ctypes.c_int
@@ -158,16 +161,16 @@ lib.rf_select_keyframes_adaptive.restype = ctypes.c_int
 _cachep = ctypes.POINTER(rf_rolling_cache)
 lib.rf_cache_store_bytes.argtypes = [_i32, _i64, _i32, _i32, ctypes.POINTER(_i64)]
 lib.rf_cache_store_bytes.restype = ctypes.c_int
-lib.rf_cache_init.argtypes = [_cachep, _vp, _vp, _i32p, _i32, _i32, _i64, _i32, _i32,
+lib.rf_cache_init.argtypes = [_cachep, _vp, _vp, _vp, _i32, _i32, _i64, _i32, _i32,
                               ctypes.c_double, _vp]
 lib.rf_cache_init.restype = ctypes.c_int
-lib.rf_cache_shift_store.argtypes = [_cachep, _vp, _vp, _i32p, _i32, ctypes.c_double, _vp]
+lib.rf_cache_shift_store.argtypes = [_cachep, _vp, _vp, _vp, _i32, ctypes.c_double, _vp]
 lib.rf_cache_shift_store.restype = ctypes.c_int
 lib.rf_cache_alpha.argtypes = [_cachep, _i32, ctypes.c_double, _dp]
 lib.rf_cache_alpha.restype = ctypes.c_int
-lib.rf_cache_project_kv.argtypes = [_cachep, _vp, _vp, _vp, _i32p, _i32, ctypes.c_double, _vp]
+lib.rf_cache_project_kv.argtypes = [_cachep, _vp, _vp, _vp, _vp, _i32, ctypes.c_double, _vp]
 lib.rf_cache_project_kv.restype = ctypes.c_int
-lib.rf_keyframe_attention_cached.argtypes = [_vp, _vp, _vp, _vp, _i32p, _i32, _i32, _i32, _i32, _i32, _i32, _i32,
+lib.rf_keyframe_attention_cached.argtypes = [_vp, _vp, _vp, _vp, _vp, _i32, _i32, _i32, _i32, _i32, _i32, _i32,
                                              _cachep, _vp, ctypes.c_double, _vp, _i64, _vp]
 lib.rf_keyframe_attention_cached.restype = ctypes.c_int
 lib.rf_async_schedule.argtypes = [_i32, _i32, _i32, _i32, _i32, ctypes.POINTER(rf_step_plan), _i32p, _i32p]
@@ -186,17 +189,38 @@ def _check(status: int):
         raise RhymeFlowError(status, f"{lib.rf_status_string(status).decode()}: {msg}")
 
 
+# Addresses are passed as plain ints, and what a caller's loop passes every step
+# (int32 id arrays, uint8 masks, torch's current stream) goes through without a
+# copy or a ctypes pointer object: at the smallest sizes a call costs more on the
+# host than on the GPU (a skipped step of 5 frames of 8 x 8 tokens: 31.6 us of
+# three calls before that, 22.4 now, of which 10 are the launches themselves).
+
+def _fits(values, dtype) -> bool:
+    """values is a plain aligned contiguous 1-D array of dtype already."""
+    return type(values) is np.ndarray and values.dtype == dtype and values.ndim == 1 and values.flags.carray
+
+
+def _array(values, dtype):
+    return values if _fits(values, dtype) else np.ascontiguousarray(np.asarray(values, dtype=dtype))
+
+
+def _addr(a: np.ndarray) -> int:
+    """The address of an array's data, valid while the array lives."""
+    return a.__array_interface__["data"][0]
+
+
 def _ids(ids):
-    a = np.ascontiguousarray(np.asarray(list(ids), dtype=np.int32))
-    return a, a.ctypes.data_as(_i32p)
+    """(ids as an int32 array, its address): hold the array until the call returns."""
+    a = ids if _fits(ids, _I32) else np.ascontiguousarray(np.asarray(list(ids), dtype=np.int32))
+    return a, _addr(a)
 
 
 def _stream(stream):
     if stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
-        return ctypes.c_void_p(stream.cuda_stream)
-    return ctypes.c_void_p(int(stream))
+        return stream.cuda_stream
+    return int(stream)
 
 
 def _torch_stream(stream):
@@ -229,7 +253,7 @@ def _dev(t: torch.Tensor, name: str):
         raise ValueError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _dtype_code(dt):
@@ -312,12 +336,12 @@ def rf_project_latents(latents: torch.Tensor, timesteps, keyframe_mask, out=None
         out = _empty((B, C, T, Hl, Wl), latents.dtype, latents.device, stream)
     if out.dtype != latents.dtype or out.numel() != B * C * T * Hl * Wl:
         raise ValueError("out must match latents' dtype and [B][C][T][Hl][Wl] size")
-    ts = (ctypes.c_double * 3)(*[float(x) for x in timesteps])
-    mask = np.ascontiguousarray(np.asarray(keyframe_mask, dtype=np.uint8))
+    ts = _double3(*[float(x) for x in timesteps])
+    mask = _array(keyframe_mask, _U8)
     if mask.size != T:
         raise ValueError("keyframe_mask must have T entries")
     _check(lib.rf_project_latents(_dev(latents, "latents"), _dev(out, "out"), ts,
-                                  mask.ctypes.data_as(_u8p), B, C, T, Hl, Wl,
+                                  _addr(mask), B, C, T, Hl, Wl,
                                   _dtype_code(latents.dtype), _stream(stream)))
     return out
 
