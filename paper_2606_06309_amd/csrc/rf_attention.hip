@@ -46,9 +46,10 @@
 //  * Small launches (when the caller provides a workspace or names the static
 //    scratch): attn_bf16_small_kernel, 32 rows a workgroup, the keys shared out
 //    among its waves; the rule is at small_pays.
-//  * Frame-level key/value mask (the frame-list form): the key loop walks a list
-//    of frames in key tiles that never cross a frame; masked frames are
-//    never read.
+//  * Frame-level key/value mask (the frame-list form): the key loop walks the
+//    listed frames' keys end to end, a tile that reaches past a frame taking its
+//    last keys from the next listed one (in tiles that never cross a frame where
+//    that does not pay or fit: list_walk); masked frames are never read.
 //  * Projected keys and values at a skipped step (the cache form; App. B.2):
 //    the key loop walks all frames in frame-aligned tiles; a tile of a cached
 //    frame loads that frame's two cached hidden states h_before and h_after
@@ -135,11 +136,13 @@ struct AttnKArgs {
     float *ws_ml;           // [tail tile * split + part][kBr][2] reference max (log2 domain), row sum
     float scale_log2;   // log2(e) / sqrt(d)
     int32_t kf[kMaxFrames];
-    // key/value frame list (frame-masked form only): the keys are the tokens
-    // of frames kvf[0..n_kv), walked frame by frame in tiles that never cross
-    // a frame (tiles_per_frame = ceil(N / key tile); a frame's last tile is partial)
+    // key/value frame list: the keys are the tokens of frames kvf[0..n_kv), in
+    // list_tiles key tiles: end to end (tiles_per_frame = 0; a tile may run from
+    // one frame into the next listed one), or in tiles that never cross a frame
+    // (ceil(N / key tile) a frame, its last one partial; always in the cache form)
     int32_t n_kv;
     int32_t tiles_per_frame;
+    int32_t list_tiles;
     // frame-list form: the listed frames; cache form (all T frames walked): per
     // frame the two cache slots (h_before | h_after << 16), or -1 when the frame
     // takes its keys and values from k and v
@@ -307,6 +310,60 @@ __device__ __forceinline__ void fragment_offsets(int lane, int (&kofs)[D / 16], 
         vofs[db] = rr * L::kRow + (((2 * db + g16) ^ (L::vswz(rr) / 2)) * 32) + 8 * (j % 4);
 }
 
+// A tile of a frame list: its first key's token, its valid keys, and the key
+// from which its keys belong to the next listed frame, `delta` bytes further on
+// than consecutive tokens would be (0: none, or the frames are neighbours).
+struct ListTile {
+    int64_t tok0;
+    int32_t valid, first, delta;
+};
+// The tiles of a frame list one after the other from tile t on, without a division
+// or a wait for a frame id at each: the id of the frame after the current one is
+// fetched when the current one is entered, long before a tile reaches it (with
+// both at every tile: 500 us where this takes 490, 6 frames of 30 x 52, 12 x 128).
+template <int kBc>
+struct ListWalker {
+    int64_t o;             // the next tile's offset in its frame
+    int32_t m;             // and that frame's place in the list
+    int32_t frame, next;   // ids of frames m and m + 1 (next: any listed one after the last)
+    __device__ __forceinline__ ListWalker(const AttnKArgs &a, int64_t t) {
+        if (a.tiles_per_frame > 0) {
+            m = static_cast<int32_t>(t) / a.tiles_per_frame;
+            o = (t - static_cast<int64_t>(m) * a.tiles_per_frame) * kBc;
+        } else {
+            m = static_cast<int32_t>(t) * kBc / static_cast<int32_t>(a.N);
+            o = t * kBc - m * a.N;
+        }
+        frame = a.kvf[m];
+        next = a.kvf[m + 1 < a.n_kv ? m + 1 : m];
+    }
+    __device__ __forceinline__ ListTile take(const AttnKArgs &a, int64_t rs) {
+        ListTile g;
+        const int64_t left = a.N - o;   // keys of this frame from here on
+        g.tok0 = frame * a.N + o;
+        g.first = kBc;
+        g.delta = 0;
+        g.valid = static_cast<int32_t>(left < kBc ? left : kBc);
+        o += kBc;
+        if (o >= a.N) {
+            o = 0;
+            if (a.tiles_per_frame == 0) {
+                o = kBc - left;
+                if (o > 0 && m + 1 < a.n_kv) {
+                    g.first = static_cast<int32_t>(left);
+                    g.valid = kBc;
+                    // (a frame holds a tile: the next one does not end before this tile does)
+                    g.delta = static_cast<int32_t>((next - frame - 1) * a.N * rs * 2);
+                }
+            }
+            ++m;
+            frame = next;
+            next = a.kvf[m + 1 < a.n_kv ? m + 1 : a.n_kv - 1];
+        }
+        return g;
+    }
+};
+
 // Per-tile pipeline, double-buffered LDS, one barrier per tile:
 //   issue the global->LDS loads of tile t+1 into the buffer tile t-1 used
 //   math on tile t
@@ -321,7 +378,7 @@ __device__ __forceinline__ void fragment_offsets(int lane, int (&kofs)[D / 16], 
 template <int D, int kForm>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void attn_bf16_kernel(const AttnKArgs a) {
-    constexpr bool kKvList = kForm != kFormDense;   // frame-aligned tiles
+    constexpr bool kKvList = kForm != kFormDense;   // a frame list's tiles
     using L = TileLayout<D>;
     constexpr int kBc = L::kBc;
     constexpr int kNB = kBc / 32;                       // 32-key score blocks per tile
@@ -391,28 +448,41 @@ void attn_bf16_kernel(const AttnKArgs a) {
     struct Geom {
         int64_t tok0, left;
         int32_t valid;
+        int32_t first, delta;   // frame list: ListTile's
         int32_t slots;
         int64_t frame_off;
         float alpha;
     };
+    int64_t t_begin = 0, t_end = kKvList ? a.list_tiles : (a.S + kBc - 1) / kBc;
+    if (part >= 0) {
+        t_begin = static_cast<int64_t>(part) * a.kv_per_split;
+        if (t_begin + a.kv_per_split < t_end) t_end = t_begin + a.kv_per_split;
+    }
+    [[maybe_unused]] auto walker = [&]() {
+        if constexpr (kForm == kFormFrames) return ListWalker<kBc>(a, t_begin);
+        else return 0;
+    }();
     auto geom = [&](int64_t t) {
         Geom g;
         g.slots = -1;
         g.frame_off = 0;
         g.alpha = 0.0f;
-        if constexpr (kKvList) {
+        if constexpr (kForm == kFormCache) {
             const int32_t m = static_cast<int32_t>(t) / a.tiles_per_frame;
             const int64_t o = (t - static_cast<int64_t>(m) * a.tiles_per_frame) * kBc;
-            if constexpr (kForm == kFormCache) {
-                g.tok0 = static_cast<int64_t>(m) * a.N + o;
-                g.slots = a.kvf[m];
-                g.frame_off = o;
-                g.alpha = a.calpha[m];
-            } else {
-                g.tok0 = static_cast<int64_t>(a.kvf[m]) * a.N + o;
-            }
+            g.tok0 = static_cast<int64_t>(m) * a.N + o;
+            g.slots = a.kvf[m];
+            g.frame_off = o;
+            g.alpha = a.calpha[m];
             g.valid = static_cast<int32_t>(a.N - o < kBc ? a.N - o : kBc);
             g.left = ((g.valid - 1) * rs + D) * 2;
+        } else if constexpr (kForm == kFormFrames) {
+            const ListTile l = walker.take(a, rs);   // (called tile after tile)
+            g.tok0 = l.tok0;
+            g.valid = l.valid;
+            g.first = l.first;
+            g.delta = l.delta;
+            g.left = ((g.valid - 1) * rs + D) * 2 + l.delta;
         } else {
             g.tok0 = t * kBc;
             g.left = head_bytes - g.tok0 * rs * 2;
@@ -449,6 +519,19 @@ void attn_bf16_kernel(const AttnKArgs a) {
             __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(kbase + g.tok0 * rs), 0, rec, kBufferWord3);
         const __amdgpu_buffer_rsrc_t vr =
             __builtin_amdgcn_make_buffer_rsrc(uniform_ptr(vbase + g.tok0 * rs), 0, rec, kBufferWord3);
+        if constexpr (kForm == kFormFrames) {
+            if (g.delta != 0) {
+#pragma unroll
+                for (int i = 0; i < kLoadsPerWave; ++i) {
+                    const int chunk = (wave * kLoadsPerWave + i) * 1024;
+                    const int key = (wave * kLoadsPerWave + i) * L::kRowsPerLoad + lane / L::kSlots;
+                    const int next = key >= g.first ? g.delta : 0;
+                    load_lds16(kr, (lds_void_t *)(kdst + chunk), kgo[i] + next);
+                    load_lds16(vr, (lds_void_t *)(vdst + chunk), vgo[i] + next);
+                }
+                return;
+            }
+        }
 #pragma unroll
         for (int i = 0; i < kLoadsPerWave; ++i) {
             const int chunk = (wave * kLoadsPerWave + i) * 1024;
@@ -582,12 +665,6 @@ void attn_bf16_kernel(const AttnKArgs a) {
         __syncthreads();
     };
 
-    const int64_t ntiles = kKvList ? static_cast<int64_t>(a.n_kv) * a.tiles_per_frame : (a.S + kBc - 1) / kBc;
-    int64_t t_begin = 0, t_end = ntiles;
-    if (part >= 0) {
-        t_begin = static_cast<int64_t>(part) * a.kv_per_split;
-        t_end = t_begin + a.kv_per_split < ntiles ? t_begin + a.kv_per_split : ntiles;
-    }
     Geom cur = geom(t_begin);
     issue(cur, k0, v0);
     tile_done();
@@ -788,7 +865,7 @@ void attn_bf16_small_kernel(const AttnKArgs a) {
         for (int i = 0; i < kLoads; ++i) load_lds16(r, (lds_void_t *)(dst + i * 1024), go[i]);
     };
 
-    const int64_t n = kFrames ? static_cast<int64_t>(a.n_kv) * a.tiles_per_frame : (a.S + kBc - 1) / kBc;
+    const int64_t n = kFrames ? a.list_tiles : (a.S + kBc - 1) / kBc;
     if (wave < n) {
         Geom g = geom(wave);
         issue(g, a.k, kgo, kb);
@@ -983,15 +1060,40 @@ AttnSplit attention_split(int64_t Mq, int32_t heads, int32_t head_dim, int64_t N
 // 16 x 16, 12 x 64, five keyframes (60 tiles in quarters; 480 small ones)
 // 34.5 us against 36.9; 9 of 17 x 31, 5 x 128, three (35 in sevenths; 250) 37.3
 // against 32.7; 13 of 16 x 16, 12 x 128, four (48 in fifths; 384) 36.8 against 43.9.
-bool small_pays(const AttnSplit &sp, int64_t Mq, int32_t heads, int32_t head_dim, int64_t kv_tiles, int32_t cus) {
-    const int64_t bc = small_key_tile(head_dim), keys = kv_tiles * bc;
+bool small_pays(const AttnSplit &sp, int64_t Mq, int32_t heads, int32_t head_dim, int64_t keys, int64_t small_tiles_of_keys,
+                int32_t cus) {
     const int64_t rounds = (sp.n_direct + cus - 1) / cus;
     const double tail = sp.split > 0 ? static_cast<double>((sp.n_tail * sp.split + cus - 1) / cus) / sp.split : 0.0;
     const double whole = (rounds + tail) * keys + (sp.split > 0 ? 400.0 : 0.0);
     const int64_t small_tiles = (Mq + kSmallRows - 1) / kSmallRows * heads;
     const int64_t small_rounds = (small_tiles + cus - 1) / cus;
-    const int64_t small_keys = (kv_tiles + kWaves - 1) / kWaves * kWaves * bc;   // the wave with most tiles
+    const int64_t small_keys =   // by the wave with most tiles
+        (small_tiles_of_keys + kWaves - 1) / kWaves * kWaves * small_key_tile(head_dim);
     return small_rounds * small_keys * (head_dim == 64 ? 0.16 : 0.195) < 0.95 * whole;
+}
+
+// How a frame list's keys are cut into tiles of bc.
+struct ListWalk {
+    int64_t per_frame;   // tiles of a frame, 0: the frames' keys lie end to end
+    int64_t tiles;
+};
+
+// End to end (no partial tile but the last) where a tile meets at most two frames,
+// all offsets inside a tile fit 32 bits, and `split` equal parts are all
+// non-empty. 6 frames of 30 x 52, 12 x 128: 147 tiles of 64 instead of 150, 503 ->
+// 490 us; 5 of 30 x 52, 24 x 64: 417 -> 388; 11 of 10 x 13, 24 x 64: 55.5 -> 42.7.
+// The small kernel keeps to frames: its waves take every eighth tile, and finding
+// one by division costs it 3-5 % where no tile is saved.
+ListWalk list_walk(const AttnParams &p, int64_t bc, int64_t split) {
+    const int64_t per_frame = (p.N + bc - 1) / bc, token = static_cast<int64_t>(p.heads) * p.head_dim * 2;
+    const ListWalk aligned{per_frame, p.n_kv * per_frame};
+    if (p.N < bc || p.N > 0x3fffffffLL / p.n_kv) return aligned;
+    int64_t gap = 0;
+    for (int i = 0; i + 1 < p.n_kv; ++i) gap = p.kvf[i + 1] - p.kvf[i] - 1 > gap ? p.kvf[i + 1] - p.kvf[i] - 1 : gap;
+    if ((gap * p.N + bc) * token > 0x7fffffffLL) return aligned;
+    const int64_t tiles = (p.n_kv * p.N + bc - 1) / bc;
+    if (split > 0 && tiles <= (split - 1) * (split - 1)) return aligned;
+    return ListWalk{0, tiles};
 }
 
 hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {
@@ -1018,7 +1120,8 @@ hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {
     }
     const int64_t bc_small = small_key_tile(p.head_dim);
     const int64_t kv_small = p.n_kv > 0 ? p.n_kv * ((p.N + bc_small - 1) / bc_small) : (p.S + bc_small - 1) / bc_small;
-    const bool small = p.split_keys && !p.cache_form && small_pays(sp, Mq, p.heads, p.head_dim, kv_small, p.geo.cus);
+    const int64_t keys = p.n_kv > 0 ? list_walk(p, key_tile(p.head_dim), sp.split).tiles * key_tile(p.head_dim) : p.S;
+    const bool small = p.split_keys && !p.cache_form && small_pays(sp, Mq, p.heads, p.head_dim, keys, kv_small, p.geo.cus);
     if (small) {
         sp = AttnSplit{};
         sp.n_direct = (Mq + kSmallRows - 1) / kSmallRows * p.heads;
@@ -1044,8 +1147,17 @@ hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {
     a.scale_log2 = static_cast<float>(1.4426950408889634 / sqrt(static_cast<double>(p.head_dim)));
     for (int i = 0; i < p.M; ++i) a.kf[i] = p.kf[i];
     a.n_kv = p.n_kv;
-    a.tiles_per_frame = static_cast<int32_t>((p.N + kBc - 1) / kBc);
     for (int i = 0; i < p.n_kv; ++i) a.kvf[i] = p.kvf[i];
+    ListWalk lw{(p.N + kBc - 1) / kBc, walk * ((p.N + kBc - 1) / kBc)};
+    if (p.n_kv > 0 && small) {
+        lw.tiles = p.n_kv * lw.per_frame;
+    } else if (p.n_kv > 0) {
+        lw = list_walk(p, kBc, sp.split);
+        if (sp.split > 0) a.kv_per_split = static_cast<int32_t>((lw.tiles + sp.split - 1) / sp.split);
+    }
+    if ((p.n_kv > 0 || p.cache_form) && lw.tiles > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    a.tiles_per_frame = static_cast<int32_t>(lw.per_frame);
+    a.list_tiles = static_cast<int32_t>(lw.tiles);
     if (p.cache_form) {
         a.n_kv = walk;
         for (int i = 0; i < walk; ++i) {
@@ -1054,8 +1166,6 @@ hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {
         }
         a.store = static_cast<const uint16_t *>(p.store);
     }
-    if (a.n_kv > 0 && static_cast<int64_t>(a.n_kv) * a.tiles_per_frame > 0x7fffffffLL)
-        return hipErrorInvalidConfiguration;
     const dim3 grid(static_cast<uint32_t>(per_xcd * xcds + n_parts)), block(kThreads);
     if (small) {
         const bool frames = p.n_kv > 0;
