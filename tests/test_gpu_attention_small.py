@@ -65,6 +65,27 @@ def test_late_maxima(d):
     assert _run(w, scale_k=ramp)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_waves_that_begin_with_scores_of_minus_infinity(d):
+    """Keys 128..319 score -inf for every query: whole first tiles of some of the eight waves, whole second
+    tiles of others, none of the first 128 keys. They leave the softmax over the other keys."""
+    w = workloads.custom(5, 10, 13, 2, d, (0, 2), dtype="bf16", seed=84)
+    q, k, v = workloads.make_qkv(w, device="cuda")
+    q[..., 0] = 1.0
+    k[..., 0] = 0.0
+    k[128:320, :, 0] = -float("inf")
+    print(f"[case] small -inf scores d={d}", flush=True)
+    ws = torch.full((max(rf.rf_attention_workspace(w.M, w.T, w.T, w.H, w.W, w.heads, d, rf.RF_BF16), 64),), 0x7f,
+                    dtype=torch.uint8, device="cuda")
+    out = rf.rf_keyframe_attention_ws(q, k, v, w.keyframes, w.T, w.H, w.W, workspace=ws)
+    assert bool((ws == 0x7f).all())
+    counted = torch.cat([torch.arange(128), torch.arange(320, w.S)])
+    rows = torch.cat([torch.arange(f * w.N, (f + 1) * w.N) for f in w.keyframes])
+    qd, kd, vd = (x.cpu()[i].double().transpose(0, 1).contiguous() for x, i in ((q, rows), (k, counted), (v, counted)))
+    ref = torch.softmax(qd @ kd.transpose(1, 2).contiguous() / d ** 0.5, dim=2) @ vd
+    assert_parity(torch_bf16_to_f64(out), ref.transpose(0, 1).numpy(), "bf16", "-inf scores")
+
+
 @pytest.mark.parametrize("case", [(21, 16, 16, 12, 64, (0, 5, 10, 15, 20)), (13, 16, 16, 12, 128, (0, 4, 8, 12))],
                          ids=["d64", "d128"])
 def test_above_the_rule_the_tail_is_split(case):
