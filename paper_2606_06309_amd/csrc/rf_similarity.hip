@@ -366,9 +366,16 @@ SimGeometry similarity_geometry(int32_t B, int32_t C, int32_t T, int64_t plane) 
     // unit keep more of them in flight (5 videos of 13 frames of 61 x 105, 16
     // channels: 11.9 us against 12.7 with one); with more, the matrix instructions
     // of one wave fill a SIMD, and fewer partials are summed with one (33 frames of
-    // 90 x 160: 17.8 us against 18.8; 48 frames: 24.8 against 31.3).
+    // 90 x 160: 17.8 us against 18.8; 48 frames: 24.8 against 31.3). Where a wave
+    // then walks more than kLongWalk chunks its loads and its matrix instructions add
+    // up, and up to 36 frames, whose sums leave registers for a second wave, two
+    // workgroups overlap them (one against two, 33 frames of 90 x 160: 36 videos
+    // 272 us, 236; 12: 97.6, 88.7; 5, 17.6 chunks: 46.5, 45.2; 2, 7 chunks: 25.8,
+    // 27.0; 48 frames, 5 videos: 68, 76; 20: 242, 242).
+    constexpr int64_t kLongWalk = 16;
     const int64_t one_per_cu = kMaxWorkgroups / 2 / B > 0 ? kMaxWorkgroups / 2 / B : 1;
-    if (!wide && g.NB > 4 && g.n_runs > one_per_cu) g.n_runs = one_per_cu;
+    const bool long_walk = g.NB <= 9 && g.n_chunks * B > kLongWalk * (kMaxWorkgroups / 2) * (kThreads / 64);
+    if (!wide && g.NB > 4 && !long_walk && g.n_runs > one_per_cu) g.n_runs = one_per_cu;
     return g;
 }
 

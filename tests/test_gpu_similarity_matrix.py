@@ -48,3 +48,18 @@ def test_a_frame_without_numbers_spoils_only_its_own_entries():
     assert torch.equal(got[0][keep][:, keep], clean[0][keep][:, keep])
     assert torch.isnan(got[0, 2]).all() and torch.isnan(got[0, :, 2]).all()
     assert bool((got[0, 5][keep + [5]] == 0).all())
+
+
+@pytest.mark.parametrize("T", [33, 36, 37])
+@pytest.mark.parametrize("h", [127, 129])
+def test_batches_on_both_sides_of_the_long_walk(T, h):
+    """4 videos of 16 x h x 128: 16,256 and 16,512 chunks of 64 elements, around 16 a wave at one workgroup
+    per compute unit; 36 frames are the most that then take two."""
+    g = torch.Generator().manual_seed(T * h)
+    x = torch.randn((4, 16, T, h, 128), generator=g)
+    print(f"[case] similarity long walk T={T} h={h}", flush=True)
+    out = rf.rf_frame_similarity(x.cuda()).cpu()
+    e = x.double().transpose(1, 2).reshape(4, T, -1)
+    e = e / e.norm(dim=2, keepdim=True)
+    for b in range(4):
+        assert float((out[b] - e[b] @ e[b].t().contiguous()).abs().max()) < 16 * h * 128 * 2.0 ** -52
