@@ -646,14 +646,19 @@ void attn_bf16_kernel(const AttnKArgs a) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[b][r]);
             const float m_new = fmaxf(m_run, halves_max(mx) * sl2);
-            const float corr = fast_exp2(m_run - m_new);   // 0 on the first tile
-            m_run = m_new;
+            // a row whose scores so far are all -inf (the first tiles of the walk, or of a
+            // part of the split tail) takes 0 as its reference for this tile: its
+            // probabilities are 0 and the next tile rebases it
+            const float ref = m_new == -__builtin_huge_valf() ? 0.0f : m_new;
+            const float corr = fast_exp2(m_run - ref);   // 0 on the first tile
+            m_run = ref;
             l_run *= corr;
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) oacc[db][r] *= corr;
             ls = probs();
+            m_run = m_new;
         }
         l_run += ls;
 
@@ -746,10 +751,9 @@ constexpr int kSmallRows = 32;
 // 8 KB of K and of V a tile at either head dimension: 128 KB of LDS
 __host__ __device__ constexpr int small_key_tile(int head_dim) { return head_dim == 64 ? 64 : 32; }
 
-// The softmax of attn_bf16_kernel's tiles, but that a wave may begin with a tile of
-// scores that are all -inf: eight waves begin in eight places (there it stays inside
-// the kernel: called as this function, the compiler's schedule of its head
-// dimension 64 form loses 4 %, 1001 against 1040 TFLOP/s).
+// The softmax of attn_bf16_kernel's tiles (there it stays inside the kernel: called
+// as this function, the compiler's schedule of its head dimension 64 form loses
+// 4 %, 1001 against 1040 TFLOP/s).
 template <int D, int kNB>
 __device__ __forceinline__ void softmax_tile(f32x16_t (&sacc)[kNB], int32_t valid, int grp, float sl2, float &m_run,
                                              float &l_run, f32x16_t (&oacc)[D / 32], u32x4_t (&pw)[2 * kNB]) {
