@@ -1138,9 +1138,11 @@ hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {
     const int64_t total = sp.n_direct;
     const int64_t per_xcd = (total + xcds - 1) / xcds;
     if (nq * p.heads > 0x7fffffffLL / 64) return hipErrorInvalidConfiguration;
-    // per-lane load offsets inside a tile are 32-bit: a tile's token rows must span < 2 GiB
+    // per-lane load offsets inside a tile are 32-bit: a whole launch's tile must span < 2 GiB of
+    // token rows (a small launch's tile is half of it, but what is refused does not depend on the form)
+    if (static_cast<int64_t>(p.heads) * p.head_dim * 2 * key_tile(p.head_dim) >= 0x7fffffffLL)
+        return hipErrorInvalidConfiguration;
     const int64_t kBc = small ? small_key_tile(p.head_dim) : key_tile(p.head_dim);
-    if (static_cast<int64_t>(p.heads) * p.head_dim * 2 * kBc >= 0x7fffffffLL) return hipErrorInvalidConfiguration;
     a.n_qtiles = static_cast<int32_t>(small ? (Mq + kSmallRows - 1) / kSmallRows : nq);
     a.total_tiles = static_cast<int32_t>(total);
     a.per_xcd = static_cast<int32_t>(per_xcd);
