@@ -1,7 +1,11 @@
 """The binding's id lists and masks: every form that a caller may pass (lists,
 tuples, ranges, arrays of any integer type, stride and writability) reaches the
-library as the same numbers."""
+library as the same numbers. And the current stream, which does not depend on a
+private name of torch."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -57,3 +61,18 @@ def test_masks(mask):
 def test_an_array_that_fits_is_passed_without_a_copy():
     ids, mask = np.array(WANT, np.int32), np.array([1, 0], np.uint8)
     assert rf._ids(ids)[0] is ids and rf._array(mask, rf._U8) is mask
+
+
+def test_the_current_stream_without_torchs_private_name():
+    code = """
+import torch
+if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+    del torch._C._cuda_getCurrentRawStream
+torch.cuda.current_stream = lambda: type("Stream", (), {"cuda_stream": 1234})()
+from paper_2606_06309_amd import binding
+assert binding._stream(None) == 1234 and binding._stream(7) == 7
+print("ok")
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stderr[-2000:]
