@@ -240,7 +240,10 @@ int rf_attention_workspace(int32_t M, int32_t Mkv, int32_t T, int32_t H, int32_t
                            int32_t head_dim, int32_t dtype, int32_t compute_units, int64_t *bytes_out);
 
 /* How a bf16 attention launch is cut (rf_attention_plan). A tile is 256 query
-   rows of one head and runs as one workgroup filling one compute unit. */
+   rows of one head and runs as one workgroup filling one compute unit. Where
+   shared_keys is 1 (bf16 or fp32), a launch that may split does not run this
+   plan: it runs tiles of 32 query rows, the keys of each shared out among the
+   waves of one workgroup, and leaves the workspace alone. */
 typedef struct rf_attention_split {
     int64_t tiles;              /* ceil(M*N / 256) * heads */
     int64_t whole_tiles;        /* tiles computed over all keys in one workgroup */
@@ -249,14 +252,18 @@ typedef struct rf_attention_split {
     int32_t key_tiles_per_part; /* key tiles per part (64 keys each; 128 at head_dim 64) */
     int64_t workspace_bytes;    /* tail_tiles * parts * 256 * (4 * head_dim + 8) */
     int32_t compute_units;      /* the count the plan is made for */
-    int32_t reserved;
+    int32_t shared_keys;        /* 1: a small launch, in 32-row tiles instead (given a workspace, or _noalloc) */
 } rf_attention_split;
 
 /*
  * The split plan rf_keyframe_attention_ws / rf_frame_attention have for these
- * sizes (a small launch needs its workspace but may run without the split)
- * on compute_units compute units (arguments and errors as
- * rf_attention_workspace). For RF_F32 every count is 0 (no split).
+ * sizes on compute_units compute units (arguments and errors as
+ * rf_attention_workspace), and in shared_keys whether they run as a small launch
+ * instead, whose workspace still has to have the planned size. For RF_F32 every
+ * count is 0 (no split); shared_keys may be 1. Mkv < T: key_tiles_per_part counts
+ * key tiles that do not cross a frame; a launch that walks the listed frames' keys
+ * end to end has fewer tiles, so its parts may be shorter. shared_keys is then
+ * that of frames whose gaps span less than 2 GiB of tokens.
  */
 int rf_attention_plan(int32_t M, int32_t Mkv, int32_t T, int32_t H, int32_t W, int32_t heads, int32_t head_dim,
                       int32_t dtype, int32_t compute_units, rf_attention_split *plan_out);
@@ -271,9 +278,9 @@ int rf_attention_plan(int32_t M, int32_t Mkv, int32_t T, int32_t H, int32_t W, i
  * kv_frames = the keyframes gives the keyframe-only attention of Sec. 4's
  * ablations ("w/ keyframe-only attention"; "w/o projection", where keyframes
  * attend to the synchronised frames only). Masked frames' keys and values are
- * never read. The kernel walks the listed frames in key tiles that do not
- * cross a frame, so when N is not a multiple of 64 each frame's last tile is
- * partly idle.
+ * never read. The bf16 kernel walks the listed frames' keys end to end in key
+ * tiles; in tiles that do not cross a frame where N is below the key tile or
+ * the gaps between listed frames span 2 GiB, in small launches and in fp32.
  *
  * kv_frames [Mkv]: strictly increasing, each in [0, T), 1 <= Mkv <= T (Mkv = T
  * is rf_keyframe_attention). workspace / workspace_bytes: as

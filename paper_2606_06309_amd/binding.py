@@ -87,7 +87,7 @@ class rf_attention_split(ctypes.Structure):
         ("key_tiles_per_part", ctypes.c_int32),
         ("workspace_bytes", ctypes.c_int64),
         ("compute_units", ctypes.c_int32),
-        ("reserved", ctypes.c_int32),
+        ("shared_keys", ctypes.c_int32),
     ]
 
 
@@ -387,12 +387,23 @@ def rf_attention_workspace(M: int, Mkv: int, T: int, H: int, W: int, heads: int,
 
 def rf_attention_plan(M: int, Mkv: int, T: int, H: int, W: int, heads: int, head_dim: int, dtype,
                       compute_units: int = 0) -> dict:
-    """The split plan of a bf16 attention launch as a dict of the fields of
+    """The split plan of a bf16 attention launch as a dict of the counts of
     rf_attention_split (compute_units 0: the current device)."""
     p = rf_attention_split()
     code = dtype if isinstance(dtype, int) else _dtype_code(dtype)
     _check(lib.rf_attention_plan(M, Mkv, T, H, W, heads, head_dim, code, compute_units, ctypes.byref(p)))
-    return {name: int(getattr(p, name)) for name, _ in rf_attention_split._fields_ if name != "reserved"}
+    return {name: int(getattr(p, name)) for name, _ in rf_attention_split._fields_ if name != "shared_keys"}
+
+
+def attention_shares_keys(M: int, Mkv: int, T: int, H: int, W: int, heads: int, head_dim: int, dtype,
+                          compute_units: int = 0) -> bool:
+    """Whether an attention launch of these sizes that is given a workspace (or
+    takes the static scratch) runs in 32-row tiles whose keys are shared out,
+    instead of the split plan: rf_attention_plan's shared_keys."""
+    p = rf_attention_split()
+    code = dtype if isinstance(dtype, int) else _dtype_code(dtype)
+    _check(lib.rf_attention_plan(M, Mkv, T, H, W, heads, head_dim, code, compute_units, ctypes.byref(p)))
+    return bool(p.shared_keys)
 
 
 def _workspace(workspace, nbytes, device, stream):

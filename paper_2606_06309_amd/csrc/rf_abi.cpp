@@ -412,9 +412,9 @@ int rf_attention_plan(int32_t M, int32_t Mkv, int32_t T, int32_t H, int32_t W, i
     rf_attention_split out;
     memset(&out, 0, sizeof out);
     out.compute_units = cus;
+    rf::AttnSplit sp{};
     if (dtype == RF_BF16) {
-        const rf::AttnSplit sp = rf::attention_split(static_cast<int64_t>(M) * N, heads, head_dim, N, N * T,
-                                                     Mkv < T ? Mkv : 0, cus);
+        sp = rf::attention_split(static_cast<int64_t>(M) * N, heads, head_dim, N, N * T, Mkv < T ? Mkv : 0, cus);
         out.tiles = sp.n_tiles;
         out.whole_tiles = sp.n_direct;
         out.tail_tiles = sp.n_tail;
@@ -422,6 +422,17 @@ int rf_attention_plan(int32_t M, int32_t Mkv, int32_t T, int32_t H, int32_t W, i
         out.key_tiles_per_part = static_cast<int32_t>(sp.kv_per_split);
         out.workspace_bytes = sp.ws_bytes;
     }
+    rf::AttnParams p{};
+    p.S = N * T;
+    p.N = N;
+    p.M = M;
+    p.heads = heads;
+    p.head_dim = head_dim;
+    p.dtype = dtype;
+    p.n_kv = Mkv < T ? Mkv : 0;
+    for (int32_t i = 0; i < p.n_kv; ++i) p.kvf[i] = i;
+    p.geo.cus = cus;
+    out.shared_keys = rf::attention_shares_keys(p, sp) ? 1 : 0;
     *plan_out = out;
     return ok();
 }

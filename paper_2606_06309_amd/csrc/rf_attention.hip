@@ -1078,7 +1078,7 @@ bool small_pays(const AttnSplit &sp, int64_t Mq, int32_t heads, int32_t head_dim
     const int64_t small_rounds = (small_tiles + cus - 1) / cus;
     const int64_t small_keys =   // by the wave with most tiles
         (small_tiles_of_keys + kWaves - 1) / kWaves * kWaves * small_key_tile(head_dim);
-    return small_rounds * small_keys * (head_dim == 64 ? 0.16 : 0.195) < 0.95 * whole;
+    return static_cast<double>(small_rounds) * small_keys * (head_dim == 64 ? 0.16 : 0.195) < 0.95 * whole;
 }
 
 // How a frame list's keys are cut into tiles of bc.
@@ -1105,6 +1105,16 @@ ListWalk list_walk(const AttnParams &p, int64_t bc, int64_t split) {
     return ListWalk{0, tiles};
 }
 
+bool attention_shares_keys(const AttnParams &p, const AttnSplit &sp) {
+    const int64_t Mq = static_cast<int64_t>(p.M) * p.N;
+    if (p.cache_form) return false;
+    if (p.dtype == RF_F32) return f32_split_pays(Mq, p.heads, p.geo.cus);
+    const int64_t bc = key_tile(p.head_dim), bc_small = small_key_tile(p.head_dim);
+    const int64_t tiles = p.n_kv > 0 ? p.n_kv * ((p.N + bc_small - 1) / bc_small) : (p.S + bc_small - 1) / bc_small;
+    const int64_t keys = p.n_kv > 0 ? list_walk(p, bc, sp.split).tiles * bc : p.S;
+    return small_pays(sp, Mq, p.heads, p.head_dim, keys, tiles, p.geo.cus);
+}
+
 hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {
     const int64_t Mq = static_cast<int64_t>(p.M) * p.N;
     if (p.dtype == RF_F32) return launch_attention_f32(p, stream);
@@ -1127,10 +1137,7 @@ hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {
         sp = attention_split(Mq, p.heads, p.head_dim, p.N, p.S, p.n_kv, p.geo.cus, walk);
         if (sp.split > 0 && p.ws_bytes < sp.ws_bytes) return hipErrorInvalidValue;
     }
-    const int64_t bc_small = small_key_tile(p.head_dim);
-    const int64_t kv_small = p.n_kv > 0 ? p.n_kv * ((p.N + bc_small - 1) / bc_small) : (p.S + bc_small - 1) / bc_small;
-    const int64_t keys = p.n_kv > 0 ? list_walk(p, key_tile(p.head_dim), sp.split).tiles * key_tile(p.head_dim) : p.S;
-    const bool small = p.split_keys && !p.cache_form && small_pays(sp, Mq, p.heads, p.head_dim, keys, kv_small, p.geo.cus);
+    const bool small = p.split_keys && attention_shares_keys(p, sp);
     if (small) {
         sp = AttnSplit{};
         sp.n_direct = (Mq + kSmallRows - 1) / kSmallRows * p.heads;

@@ -418,7 +418,7 @@ hipError_t launch_attention_f32(const AttnParams &p, hipStream_t stream) {
     a.n_kv = p.n_kv;
     for (int i = 0; i < p.n_kv; ++i) a.kvf[i] = p.kvf[i];
 
-    const bool split = p.split_keys && f32_split_pays(Mq, p.heads, cus);
+    const bool split = p.split_keys && attention_shares_keys(p, AttnSplit{});
     const int64_t rows = split ? kSplitRows : kTileRows;
     const int64_t keys = split ? kSplitKeys : (p.head_dim == 128 ? kTileKeys<128> : kTileKeys<64>);
     const int64_t nq = (Mq + rows - 1) / rows;

@@ -73,6 +73,10 @@ AttnSplit attention_split(int64_t Mq, int32_t heads, int32_t head_dim, int64_t N
 
 hipError_t launch_attention(const AttnParams &p, hipStream_t stream);
 
+// Whether a launch that may (split_keys) shares out the keys of 32-row tiles
+// among the waves of a workgroup; sp is its split plan. Never in the cache form.
+bool attention_shares_keys(const AttnParams &p, const AttnSplit &sp);
+
 // The fp32 form (rf_attention_f32.hip), and whether it shares out the keys of
 // a launch of Mq query rows on `cus` compute units when split_keys allows it.
 hipError_t launch_attention_f32(const AttnParams &p, hipStream_t stream);

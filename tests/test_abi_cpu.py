@@ -225,6 +225,25 @@ def test_attention_plan_head_dim_64_and_fp32():
                      workspace_bytes=0, compute_units=256)
 
 
+# M, Mkv, T, H, W, heads, head_dim, dtype, whether the keys are shared out on 256 compute units
+SHARED = [
+    (3, 9, 9, 17, 31, 5, 64, rf.RF_BF16, True), (3, 9, 9, 17, 31, 5, 128, rf.RF_BF16, True),
+    (5, 21, 21, 16, 16, 12, 64, rf.RF_BF16, False), (4, 13, 13, 16, 16, 12, 128, rf.RF_BF16, False),
+    (1, 1, 1, 1, 1, 1, 64, rf.RF_BF16, False), (8, 33, 33, 45, 80, 24, 128, rf.RF_BF16, False),
+    (3, 6, 11, 10, 13, 3, 64, rf.RF_BF16, True), (6, 6, 21, 30, 52, 12, 128, rf.RF_BF16, False),
+    (3, 5, 5, 8, 8, 2, 64, rf.RF_F32, True), (5, 13, 13, 30, 52, 12, 128, rf.RF_F32, False),
+    # sizes whose products pass 64 bits: the choice is made in floating point
+    (256, 256, 256, 1 << 20, 1 << 22, 1, 64, rf.RF_BF16, False),
+]
+
+
+@pytest.mark.parametrize("case", SHARED, ids=lambda c: "x".join(map(str, c[:7])) + f"_{c[7]}")
+def test_small_launches_share_out_the_keys(case):
+    """Few 32-row tiles for the device end earlier than whole tiles of 256 (bf16) or 128 rows (fp32) do; the
+    cases on both sides are those whose times stand beside the rules."""
+    assert rf.attention_shares_keys(*case[:8], 256) == case[8]
+
+
 def test_attention_plan_of_the_current_device_needs_one():
     if _gpu_present():
         pytest.skip("a device is present")

@@ -22,6 +22,11 @@ def _ws():
     return torch.empty(16, dtype=torch.uint8, device="cuda")   # fp32 takes none: any buffer will do
 
 
+def _shares(w, mkv=None):
+    """Whether the launch given a workspace shares out the keys (one without a workspace never does)."""
+    return rf.attention_shares_keys(w.M, mkv or w.T, w.T, w.H, w.W, w.heads, w.head_dim, rf.RF_F32)
+
+
 # (T, H, W, heads, keyframes): keys 1, 31..33, 63..65, 127..129; query rows from 1 to 390; one wave's
 # key tile (32), one per wave (128 or 256) and one more than that
 CASES = [(1, 1, 1, 3, (0,)), (1, 1, 31, 2, (0,)), (1, 4, 8, 2, (0,)), (1, 3, 11, 2, (0,)), (3, 3, 7, 2, (0, 2)),
@@ -37,6 +42,7 @@ def test_tile_edges(case, d):
     print(f"[case] {w}", flush=True)
     q, k, v = workloads.make_qkv(w, device="cuda")
     ref = oracle.keyframe_attention(q.cpu(), k.cpu(), v.cpu(), kf, w.N)
+    assert _shares(w)
     whole = rf.rf_keyframe_attention(q, k, v, kf, T, H, W)
     split = rf.rf_keyframe_attention_ws(q, k, v, kf, T, H, W, workspace=_ws())
     assert_parity(_f64(whole), ref, "f32", "whole tiles")
@@ -55,6 +61,7 @@ def test_frame_lists(N, d):
     w = workloads.custom(6, H, W, 2, d, (0, 3, 5), dtype="f32", seed=71)
     q, k, v = workloads.make_qkv(w, device="cuda")
     kv = (1, 2, 5)
+    assert _shares(w, len(kv))
     ref = oracle.frame_attention(q.cpu(), k.cpu(), v.cpu(), w.keyframes, kv, w.N)
     k[0:w.N] = float("nan")   # a frame that is not listed is never read
     for ws in (None, _ws()):
@@ -71,6 +78,7 @@ def test_keys_with_scores_of_minus_infinity_count_nothing(d):
     q[..., 0] = 1.0
     k[..., 0] = 0.0
     k[:40, :, 0] = -float("inf")
+    assert _shares(w)
     qd, kd, vd = (x.double().transpose(0, 1).contiguous() for x in (q, k[40:], v[40:]))
     rows = torch.cat([torch.arange(f * w.N, (f + 1) * w.N) for f in w.keyframes]).cuda()
     ref = torch.softmax(qd[:, rows] @ kd.transpose(1, 2).contiguous() / d ** 0.5, dim=2) @ vd

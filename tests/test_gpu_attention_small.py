@@ -2,8 +2,8 @@
 shared out among its eight waves): sizes at the edges of the row tile and of the
 key tile, fewer key tiles than waves, one and several a wave, ragged frames in
 the frame-list form, and maxima that move late in every wave's keys. Against the
-fp64 oracle with the bf16 gates. Which launches take it is visible in the
-workspace, which it leaves alone and a split tail fills."""
+fp64 oracle with the bf16 gates. Which launches take it the plan says; the
+workspace, which a split tail fills, is left alone."""
 import numpy as np
 import pytest
 import torch
@@ -25,7 +25,12 @@ CASES = [
 ]
 
 
-def _run(w, kvf=None, scale_k=None):
+def _shares(w, mkv=None):
+    return rf.attention_shares_keys(w.M, mkv or w.T, w.T, w.H, w.W, w.heads, w.head_dim, rf.RF_BF16)
+
+
+def _run(w, kvf=None, scale_k=None, small=True):
+    assert _shares(w, len(kvf) if kvf else None) == small
     q, k, v = workloads.make_qkv(w, device="cuda")
     if scale_k is not None:
         k = (k.float() * scale_k).to(k.dtype)
@@ -65,11 +70,16 @@ def test_late_maxima(d):
     assert _run(w, scale_k=ramp)
 
 
+@pytest.mark.parametrize("T", [5, 17])
 @pytest.mark.parametrize("d", [64, 128])
-def test_waves_that_begin_with_scores_of_minus_infinity(d):
+def test_waves_that_begin_with_scores_of_minus_infinity(d, T):
     """Keys 128..319 score -inf for every query: whole first tiles of some of the eight waves, whole second
-    tiles of others, none of the first 128 keys. They leave the softmax over the other keys."""
-    w = workloads.custom(5, 10, 13, 2, d, (0, 2), dtype="bf16", seed=84)
+    tiles of others, none of the first 128 keys. They leave the softmax over the other keys. At 17 frames the
+    plan splits, so a workspace left alone shows that the plan did not run."""
+    w = workloads.custom(T, 10, 13, 2, d, (0, 2), dtype="bf16", seed=84)
+    assert _shares(w)
+    parts = rf.rf_attention_plan(w.M, w.T, w.T, w.H, w.W, w.heads, d, rf.RF_BF16)["parts"]
+    assert T == 5 or parts > 1
     q, k, v = workloads.make_qkv(w, device="cuda")
     q[..., 0] = 1.0
     k[..., 0] = 0.0
@@ -93,4 +103,4 @@ def test_above_the_rule_the_tail_is_split(case):
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("sized for 256 compute units")
     print(f"[case] split above the small rule {case}", flush=True)
-    assert not _run(workloads.custom(T, H, W, heads, d, kf, dtype="bf16", seed=83))
+    assert not _run(workloads.custom(T, H, W, heads, d, kf, dtype="bf16", seed=83), small=False)

@@ -36,7 +36,9 @@ def _run(T, H, W, heads, d, qf, kvf, forms):
     k.view(T, -1)[masked] = float("nan")
     v.view(T, -1)[masked] = float("nan")
     need = rf.rf_attention_workspace(len(qf), len(kvf), T, H, W, heads, d, rf.RF_BF16)
+    shared = rf.attention_shares_keys(len(qf), len(kvf), T, H, W, heads, d, rf.RF_BF16)
     for form in forms:
+        assert form == "whole" or shared == (form == "small")
         print(f"[case] frame walk T={T} N={w.N} heads={heads} d={d} kv={kvf} {form}", flush=True)
         if form == "whole":
             out = rf.rf_frame_attention(q, k, v, qf, kvf, T, H, W)
