@@ -61,6 +61,7 @@
 #include <atomic>
 
 #include "rf_device.h"
+#include "rf_list_walk.h"
 
 namespace rf {
 namespace {
@@ -310,60 +311,6 @@ __device__ __forceinline__ void fragment_offsets(int lane, int (&kofs)[D / 16], 
         vofs[db] = rr * L::kRow + (((2 * db + g16) ^ (L::vswz(rr) / 2)) * 32) + 8 * (j % 4);
 }
 
-// A tile of a frame list: its first key's token, its valid keys, and the key
-// from which its keys belong to the next listed frame, `delta` bytes further on
-// than consecutive tokens would be (0: none, or the frames are neighbours).
-struct ListTile {
-    int64_t tok0;
-    int32_t valid, first, delta;
-};
-// The tiles of a frame list one after the other from tile t on, without a division
-// or a wait for a frame id at each: the id of the frame after the current one is
-// fetched when the current one is entered, long before a tile reaches it (with
-// both at every tile: 500 us where this takes 490, 6 frames of 30 x 52, 12 x 128).
-template <int kBc>
-struct ListWalker {
-    int64_t o;             // the next tile's offset in its frame
-    int32_t m;             // and that frame's place in the list
-    int32_t frame, next;   // ids of frames m and m + 1 (next: any listed one after the last)
-    __device__ __forceinline__ ListWalker(const AttnKArgs &a, int64_t t) {
-        if (a.tiles_per_frame > 0) {
-            m = static_cast<int32_t>(t) / a.tiles_per_frame;
-            o = (t - static_cast<int64_t>(m) * a.tiles_per_frame) * kBc;
-        } else {
-            m = static_cast<int32_t>(t) * kBc / static_cast<int32_t>(a.N);
-            o = t * kBc - m * a.N;
-        }
-        frame = a.kvf[m];
-        next = a.kvf[m + 1 < a.n_kv ? m + 1 : m];
-    }
-    __device__ __forceinline__ ListTile take(const AttnKArgs &a, int64_t rs) {
-        ListTile g;
-        const int64_t left = a.N - o;   // keys of this frame from here on
-        g.tok0 = frame * a.N + o;
-        g.first = kBc;
-        g.delta = 0;
-        g.valid = static_cast<int32_t>(left < kBc ? left : kBc);
-        o += kBc;
-        if (o >= a.N) {
-            o = 0;
-            if (a.tiles_per_frame == 0) {
-                o = kBc - left;
-                if (o > 0 && m + 1 < a.n_kv) {
-                    g.first = static_cast<int32_t>(left);
-                    g.valid = kBc;
-                    // (a frame holds a tile: the next one does not end before this tile does)
-                    g.delta = static_cast<int32_t>((next - frame - 1) * a.N * rs * 2);
-                }
-            }
-            ++m;
-            frame = next;
-            next = a.kvf[m + 1 < a.n_kv ? m + 1 : a.n_kv - 1];
-        }
-        return g;
-    }
-};
-
 // Per-tile pipeline, double-buffered LDS, one barrier per tile:
 //   issue the global->LDS loads of tile t+1 into the buffer tile t-1 used
 //   math on tile t
@@ -459,7 +406,7 @@ void attn_bf16_kernel(const AttnKArgs a) {
         if (t_begin + a.kv_per_split < t_end) t_end = t_begin + a.kv_per_split;
     }
     [[maybe_unused]] auto walker = [&]() {
-        if constexpr (kForm == kFormFrames) return ListWalker<kBc>(a, t_begin);
+        if constexpr (kForm == kFormFrames) return ListWalker<kBc, AttnKArgs>(a, t_begin);
         else return 0;
     }();
     auto geom = [&](int64_t t) {
@@ -1080,12 +1027,6 @@ bool small_pays(const AttnSplit &sp, int64_t Mq, int32_t heads, int32_t head_dim
         (small_tiles_of_keys + kWaves - 1) / kWaves * kWaves * small_key_tile(head_dim);
     return static_cast<double>(small_rounds) * small_keys * (head_dim == 64 ? 0.16 : 0.195) < 0.95 * whole;
 }
-
-// How a frame list's keys are cut into tiles of bc.
-struct ListWalk {
-    int64_t per_frame;   // tiles of a frame, 0: the frames' keys lie end to end
-    int64_t tiles;
-};
 
 // End to end (no partial tile but the last) where a tile meets at most two frames,
 // all offsets inside a tile fit 32 bits, and `split` equal parts are all

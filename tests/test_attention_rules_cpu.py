@@ -1,6 +1,6 @@
-"""Host rules of the attention launch (which sizes are refused), called in the
-built library by a small C++ program: no GPU is used, as every launch that it
-asks for is refused first."""
+"""Host rules of the attention launch (which sizes are refused, how a frame
+list's keys are walked), called in the built library by a small C++ program: no
+GPU is used, as every launch that it asks for is refused first."""
 import os
 import shutil
 import subprocess

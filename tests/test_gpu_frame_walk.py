@@ -64,3 +64,14 @@ def test_split_tail(case):
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("sized for 256 compute units")
     _run(*case, ("whole", "split"))
+
+
+def test_split_tail_that_stays_frame_aligned():
+    """32 frames of 65 keys are 33 tiles end to end but 64 frame-aligned ones, for which the plan has 8 parts:
+    33 tiles in parts of five would leave the eighth without one, so the parts stay frame-aligned."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("sized for 256 compute units")
+    kvf = tuple(f for f in range(33) if f != 7)
+    plan = rf.rf_attention_plan(33, 32, 33, 5, 13, 32, 128, rf.RF_BF16)
+    assert (plan["tail_tiles"], plan["parts"], plan["key_tiles_per_part"]) == (32, 8, 8)
+    _run(33, 5, 13, 32, 128, tuple(range(33)), kvf, ("whole", "split"))
