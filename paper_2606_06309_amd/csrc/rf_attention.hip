@@ -1007,25 +1007,46 @@ AttnSplit attention_split(int64_t Mq, int32_t heads, int32_t head_dim, int64_t N
     return sp;
 }
 
-// Whether the small kernel ends earlier than whole tiles and a split tail.
-// Both are counted in keys walked by a CU's eight waves over 256 rows, 16.3 ns a
-// key at head dimension 64 and 27 at 128: whole rounds of all keys, the tail's
-// share of a round and, for the parts' results and their combine, about 400 keys;
-// against rounds of 32-row workgroups, each at 2.6 ns a key (0.16) or 5.3 (0.195;
-// 0.125 would be an eighth). Measured, split against small kernel: 21 frames of
-// 16 x 16, 12 x 64, five keyframes (60 tiles in quarters; 480 small ones)
-// 34.5 us against 36.9; 9 of 17 x 31, 5 x 128, three (35 in sevenths; 250) 37.3
-// against 32.7; 13 of 16 x 16, 12 x 128, four (48 in fifths; 384) 36.8 against 43.9.
-bool small_pays(const AttnSplit &sp, int64_t Mq, int32_t heads, int32_t head_dim, int64_t keys, int64_t small_tiles_of_keys,
-                int32_t cus) {
-    const int64_t rounds = (sp.n_direct + cus - 1) / cus;
-    const double tail = sp.split > 0 ? static_cast<double>((sp.n_tail * sp.split + cus - 1) / cus) / sp.split : 0.0;
-    const double whole = (rounds + tail) * keys + (sp.split > 0 ? 400.0 : 0.0);
+// Whether the small kernel ends earlier than whole tiles and a split tail, by their
+// times in us, counted in rounds of the device: a round of whole tiles has a fixed
+// part, which grows with the rows that its tiles hold, and the time of each key tile
+// walked; a split has a second kernel and the parts' results, written and read again;
+// a round of small tiles has a fixed part and the tiles of its busiest wave. The
+// counts are fitted to the times of both at 4,300 drawn launches (1 to 33 frames of up
+// to 2,048 tokens, 1 to 48 heads, dense and frame lists, most of them ragged; rms
+// error 7-8 %), and the small kernel has to come out 7 % shorter: of 2,681 that then
+// take it six are behind by more than 4 % (9 at most; without the fixed parts 314
+// were, by up to 94 %), and the choice loses 0.6 % to the better of the two on average.
+// Whole tiles against small ones, us:
+//   9 frames of 17 x 31, 5 x 128, three keyframes (35 in sevenths; 250)   37.3   32.7
+//   21 of 16 x 16, 12 x 64, five (60 in quarters; 480)                    34.5   36.9
+//   13 of 16 x 16, 12 x 128, four (48 in fifths; 384)                     36.8   43.9
+//   3 of 22 x 13, 31 x 64, two (93; 558)                                  19.6   20.6
+//   5 of 10 x 14, 43 x 128, four (129; 774 in four rounds)                25.1   34.9
+//   one listed of 2 of 21 x 47, 40 x 64, one (160; 1,240 in five)         22.8   33.6
+struct SmallCost {
+    double round, rows, tile;                // whole tiles: a round, the more of it at full rows, a key tile
+    double split, parts;                     // a split: the second kernel, 256 parts' results
+    double small, small_round, small_tile;   // small tiles: the launch's difference, a round, a wave's key tile
+};
+constexpr SmallCost kSmallCost64{4.4, 2.1, 1.90, 2.9, 4.9, 1.0, 3.3, 1.30};
+constexpr SmallCost kSmallCost128{4.1, 4.8, 1.50, 1.9, 9.5, 0.4, 4.6, 1.25};
+constexpr double kSmallShorter = 0.93;
+
+bool small_pays(const AttnSplit &sp, int64_t Mq, int32_t heads, int32_t head_dim, int64_t key_tiles,
+                int64_t small_key_tiles, int32_t cus) {
+    const SmallCost &c = head_dim == 64 ? kSmallCost64 : kSmallCost128;
+    const int64_t parts = sp.n_tail * sp.split;
+    const double rounds = static_cast<double>((sp.n_direct + cus - 1) / cus);
+    const double part_rounds = static_cast<double>((parts + cus - 1) / cus);
+    const double walks = rounds + (sp.split > 0 ? part_rounds / sp.split : 0.0);   // of all keys
+    const double rows = Mq < kBr ? static_cast<double>(Mq) / kBr : 1.0;            // of a tile's
+    const double whole = (rounds + part_rounds) * (c.round + c.rows * rows) + walks * key_tiles * c.tile +
+                         (sp.split > 0 ? c.split + c.parts * parts / 256 : 0.0);
     const int64_t small_tiles = (Mq + kSmallRows - 1) / kSmallRows * heads;
-    const int64_t small_rounds = (small_tiles + cus - 1) / cus;
-    const int64_t small_keys =   // by the wave with most tiles
-        (small_tiles_of_keys + kWaves - 1) / kWaves * kWaves * small_key_tile(head_dim);
-    return static_cast<double>(small_rounds) * small_keys * (head_dim == 64 ? 0.16 : 0.195) < 0.95 * whole;
+    const double small_rounds = static_cast<double>((small_tiles + cus - 1) / cus);
+    const double wave_tiles = static_cast<double>((small_key_tiles + kWaves - 1) / kWaves);
+    return c.small + small_rounds * (c.small_round + c.small_tile * wave_tiles) < kSmallShorter * whole;
 }
 
 // End to end (no partial tile but the last) where a tile meets at most two frames,
@@ -1051,9 +1072,10 @@ bool attention_shares_keys(const AttnParams &p, const AttnSplit &sp) {
     if (p.cache_form) return false;
     if (p.dtype == RF_F32) return f32_split_pays(Mq, p.heads, p.geo.cus);
     const int64_t bc = key_tile(p.head_dim), bc_small = small_key_tile(p.head_dim);
-    const int64_t tiles = p.n_kv > 0 ? p.n_kv * ((p.N + bc_small - 1) / bc_small) : (p.S + bc_small - 1) / bc_small;
-    const int64_t keys = p.n_kv > 0 ? list_walk(p, bc, sp.split).tiles * bc : p.S;
-    return small_pays(sp, Mq, p.heads, p.head_dim, keys, tiles, p.geo.cus);
+    const int64_t small_tiles =
+        p.n_kv > 0 ? p.n_kv * ((p.N + bc_small - 1) / bc_small) : (p.S + bc_small - 1) / bc_small;
+    const int64_t tiles = p.n_kv > 0 ? list_walk(p, bc, sp.split).tiles : (p.S + bc - 1) / bc;
+    return small_pays(sp, Mq, p.heads, p.head_dim, tiles, small_tiles, p.geo.cus);
 }
 
 hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {

@@ -229,8 +229,12 @@ def test_attention_plan_head_dim_64_and_fp32():
 SHARED = [
     (3, 9, 9, 17, 31, 5, 64, rf.RF_BF16, True), (3, 9, 9, 17, 31, 5, 128, rf.RF_BF16, True),
     (5, 21, 21, 16, 16, 12, 64, rf.RF_BF16, False), (4, 13, 13, 16, 16, 12, 128, rf.RF_BF16, False),
-    (1, 1, 1, 1, 1, 1, 64, rf.RF_BF16, False), (8, 33, 33, 45, 80, 24, 128, rf.RF_BF16, False),
+    (1, 1, 1, 1, 1, 1, 64, rf.RF_BF16, True), (8, 33, 33, 45, 80, 24, 128, rf.RF_BF16, False),
     (3, 6, 11, 10, 13, 3, 64, rf.RF_BF16, True), (6, 6, 21, 30, 52, 12, 128, rf.RF_BF16, False),
+    # few keys and many 32-row tiles: each of their rounds has a fixed part that whole tiles have once
+    (4, 5, 5, 10, 14, 43, 128, rf.RF_BF16, False), (1, 1, 2, 21, 47, 40, 64, rf.RF_BF16, False),
+    (2, 3, 3, 22, 13, 31, 64, rf.RF_BF16, False), (3, 1, 23, 13, 19, 22, 128, rf.RF_BF16, False),
+    (29, 31, 31, 2, 37, 17, 64, rf.RF_BF16, False), (2, 27, 27, 7, 12, 43, 128, rf.RF_BF16, False),
     (3, 5, 5, 8, 8, 2, 64, rf.RF_F32, True), (5, 13, 13, 30, 52, 12, 128, rf.RF_F32, False),
     # sizes whose products pass 64 bits: the choice is made in floating point
     (256, 256, 256, 1 << 20, 1 << 22, 1, 64, rf.RF_BF16, False),
