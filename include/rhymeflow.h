@@ -279,8 +279,9 @@ int rf_attention_plan(int32_t M, int32_t Mkv, int32_t T, int32_t H, int32_t W, i
  * ablations ("w/ keyframe-only attention"; "w/o projection", where keyframes
  * attend to the synchronised frames only). Masked frames' keys and values are
  * never read. The bf16 kernel walks the listed frames' keys end to end in key
- * tiles; in tiles that do not cross a frame where N is below the key tile or
- * the gaps between listed frames span 2 GiB, in small launches and in fp32.
+ * tiles; in tiles that do not cross a frame where that takes no more tiles, where
+ * N is below the key tile or the gaps between listed frames span 2 GiB, in small
+ * launches and in fp32.
  *
  * kv_frames [Mkv]: strictly increasing, each in [0, T), 1 <= Mkv <= T (Mkv = T
  * is rf_keyframe_attention). workspace / workspace_bytes: as

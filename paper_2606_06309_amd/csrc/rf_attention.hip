@@ -157,8 +157,9 @@ static_assert(sizeof(AttnKArgs) <= 4096, "attention kernel arguments exceed 4 KB
 
 // Forms of the bf16 kernel's key loop.
 constexpr int kFormDense = 0;    // all S tokens in order
-constexpr int kFormFrames = 1;   // the tokens of the listed frames a.kvf
+constexpr int kFormFrames = 1;   // the tokens of the listed frames a.kvf, end to end
 constexpr int kFormCache = 2;    // all frames; cached frames give projected keys = values
+constexpr int kFormAligned = 3;  // the tokens of the listed frames, in tiles that never cross a frame
 
 // Two floats -> two bf16 (round to nearest even) packed low-first in a word.
 __device__ inline uint32_t pack_bf16x2(float lo, float hi) {
@@ -320,8 +321,8 @@ __device__ __forceinline__ void fragment_offsets(int lane, int (&kofs)[D / 16], 
 // range check zero-fills the keys past it (keys >= S, or past the end of a
 // frame in the frame-masked form) and their scores are masked. The loop is
 // unrolled by two so every LDS access names its buffer statically.
-// kForm: kFormDense, kFormFrames (the keys are the tokens of the frames a.kvf,
-// a frame-level mask) or kFormCache (every frame, cached frames projected).
+// kForm: kFormDense, kFormFrames or kFormAligned (the keys are the tokens of the
+// frames a.kvf, a frame-level mask) or kFormCache (every frame, cached frames projected).
 template <int D, int kForm>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2)))
 void attn_bf16_kernel(const AttnKArgs a) {
@@ -422,6 +423,11 @@ void attn_bf16_kernel(const AttnKArgs a) {
             g.frame_off = o;
             g.alpha = a.calpha[m];
             g.valid = static_cast<int32_t>(a.N - o < kBc ? a.N - o : kBc);
+            g.left = ((g.valid - 1) * rs + D) * 2;
+        } else if constexpr (kForm == kFormAligned) {
+            const ListTile l = aligned_tile<kBc>(a, t);
+            g.tok0 = l.tok0;
+            g.valid = l.valid;
             g.left = ((g.valid - 1) * rs + D) * 2;
         } else if constexpr (kForm == kFormFrames) {
             const ListTile l = walker.take(a, rs);   // (called tile after tile)
@@ -1049,10 +1055,13 @@ bool small_pays(const AttnSplit &sp, int64_t Mq, int32_t heads, int32_t head_dim
     return c.small + small_rounds * (c.small_round + c.small_tile * wave_tiles) < kSmallShorter * whole;
 }
 
-// End to end (no partial tile but the last) where a tile meets at most two frames,
-// all offsets inside a tile fit 32 bits, and `split` equal parts are all
-// non-empty. 6 frames of 30 x 52, 12 x 128: 147 tiles of 64 instead of 150, 503 ->
-// 490 us; 5 of 30 x 52, 24 x 64: 417 -> 388; 11 of 10 x 13, 24 x 64: 55.5 -> 42.7.
+// End to end (no partial tile but the last) where that saves a tile, a tile meets at
+// most two frames, all offsets inside a tile fit 32 bits, and `split` equal parts are
+// all non-empty. 6 frames of 30 x 52, 12 x 128: 147 tiles of 64 instead of 150, 489 ->
+// 480 us; 5 of 30 x 52, 24 x 64: 417 -> 388; 11 of 10 x 13, 24 x 64: 55.5 -> 42.7.
+// Where it saves none the walk alone costs 1-2 %: 10 of 16 x 16, 24 x 64, without
+// splitting: 43.8 us aligned, 44.5 end to end; 3 of 64 x 64, 4 x 128: 272, 275.5; one
+// of 1 x 22, 31 x 128: 5.8, 6.0.
 // The small kernel keeps to frames: its waves take every eighth tile, and finding
 // one by division costs it 3-5 % where no tile is saved.
 ListWalk list_walk(const AttnParams &p, int64_t bc, int64_t split) {
@@ -1063,6 +1072,7 @@ ListWalk list_walk(const AttnParams &p, int64_t bc, int64_t split) {
     for (int i = 0; i + 1 < p.n_kv; ++i) gap = p.kvf[i + 1] - p.kvf[i] - 1 > gap ? p.kvf[i + 1] - p.kvf[i] - 1 : gap;
     if ((gap * p.N + bc) * token > 0x7fffffffLL) return aligned;
     const int64_t tiles = (p.n_kv * p.N + bc - 1) / bc;
+    if (tiles == aligned.tiles) return aligned;
     if (split > 0 && tiles <= (split - 1) * (split - 1)) return aligned;
     return ListWalk{0, tiles};
 }
@@ -1157,6 +1167,9 @@ hipError_t launch_attention(const AttnParams &p, hipStream_t stream) {
     } else if (p.cache_form) {
         if (p.head_dim == 128) hipLaunchKernelGGL((attn_bf16_kernel<128, kFormCache>), grid, block, 0, stream, a);
         else hipLaunchKernelGGL((attn_bf16_kernel<64, kFormCache>), grid, block, 0, stream, a);
+    } else if (p.n_kv > 0 && a.tiles_per_frame > 0) {
+        if (p.head_dim == 128) hipLaunchKernelGGL((attn_bf16_kernel<128, kFormAligned>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((attn_bf16_kernel<64, kFormAligned>), grid, block, 0, stream, a);
     } else if (p.n_kv > 0) {
         if (p.head_dim == 128) hipLaunchKernelGGL((attn_bf16_kernel<128, kFormFrames>), grid, block, 0, stream, a);
         else hipLaunchKernelGGL((attn_bf16_kernel<64, kFormFrames>), grid, block, 0, stream, a);

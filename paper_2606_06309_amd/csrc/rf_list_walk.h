@@ -23,24 +23,28 @@ struct ListTile {
     int64_t tok0;
     int32_t valid, first, delta;
 };
-// The tiles of a frame list one after the other from tile t on, without a division
-// or a wait for a frame id at each: the id of the frame after the current one is
-// fetched when the current one is entered, long before a tile reaches it (with
-// both at every tile: 500 us where this takes 490, 6 frames of 30 x 52, 12 x 128).
+// Tile t of a list walked in tiles that never cross a frame.
 // Args: the fields N, n_kv, tiles_per_frame and kvf of AttnKArgs.
+template <int kBc, class Args>
+__host__ __device__ __forceinline__ ListTile aligned_tile(const Args &a, int64_t t) {
+    const int32_t m = static_cast<int32_t>(t) / a.tiles_per_frame;
+    const int64_t o = (t - static_cast<int64_t>(m) * a.tiles_per_frame) * kBc;
+    return ListTile{static_cast<int64_t>(a.kvf[m]) * a.N + o, static_cast<int32_t>(a.N - o < kBc ? a.N - o : kBc),
+                    kBc, 0};
+}
+
+// The tiles of a list walked end to end, one after the other from tile t on, without
+// a division or a wait for a frame id at each: the id of the frame after the current
+// one is fetched when the current one is entered, long before a tile reaches it (with
+// both at every tile: 500 us where this takes 490, 6 frames of 30 x 52, 12 x 128).
 template <int kBc, class Args>
 struct ListWalker {
     int64_t o;             // the next tile's offset in its frame
     int32_t m;             // and that frame's place in the list
     int32_t frame, next;   // ids of frames m and m + 1 (next: any listed one after the last)
     __host__ __device__ __forceinline__ ListWalker(const Args &a, int64_t t) {
-        if (a.tiles_per_frame > 0) {
-            m = static_cast<int32_t>(t) / a.tiles_per_frame;
-            o = (t - static_cast<int64_t>(m) * a.tiles_per_frame) * kBc;
-        } else {
-            m = static_cast<int32_t>(t) * kBc / static_cast<int32_t>(a.N);
-            o = t * kBc - m * a.N;
-        }
+        m = static_cast<int32_t>(t) * kBc / static_cast<int32_t>(a.N);
+        o = t * kBc - m * a.N;
         frame = a.kvf[m];
         next = a.kvf[m + 1 < a.n_kv ? m + 1 : m];
     }
@@ -52,16 +56,13 @@ struct ListWalker {
         g.delta = 0;
         g.valid = static_cast<int32_t>(left < kBc ? left : kBc);
         o += kBc;
-        if (o >= a.N) {
-            o = 0;
-            if (a.tiles_per_frame == 0) {
-                o = kBc - left;
-                if (o > 0 && m + 1 < a.n_kv) {
-                    g.first = static_cast<int32_t>(left);
-                    g.valid = kBc;
-                    // (a frame holds a tile: the next one does not end before this tile does)
-                    g.delta = static_cast<int32_t>((next - frame - 1) * a.N * rs * 2);
-                }
+        if (__builtin_expect(o >= a.N, 0)) {   // (out of the common tile's way: 527 us against 533)
+            o = kBc - left;
+            if (o > 0 && m + 1 < a.n_kv) {
+                g.first = static_cast<int32_t>(left);
+                g.valid = kBc;
+                // (a frame holds a tile: the next one does not end before this tile does)
+                g.delta = static_cast<int32_t>((next - frame - 1) * a.N * rs * 2);
             }
             ++m;
             frame = next;

@@ -76,9 +76,11 @@ static int walk(const rf::AttnParams &p, int64_t split, bool end_to_end) {
     for (int64_t part = 0; part < parts; ++part) {
         const int64_t begin = part * step, end = begin + step < lw.tiles ? begin + step : lw.tiles;
         CHECK(begin < end);
-        rf::ListWalker<kBc, WalkArgs> walker(a, begin);
+        WalkArgs e = a;
+        e.n_kv = end_to_end ? a.n_kv : 1;   // (the walker is made for walks end to end only)
+        rf::ListWalker<kBc, WalkArgs> walker(e, end_to_end ? begin : 0);
         for (int64_t t = begin; t < end; ++t) {
-            const rf::ListTile g = walker.take(a, rs);
+            const rf::ListTile g = end_to_end ? walker.take(a, rs) : rf::aligned_tile<kBc>(a, t);
             CHECK(g.valid > 0 && g.valid <= kBc);
             CHECK(g.delta >= 0 && (kBc * rs) * 2 + g.delta <= 0x7fffffffLL);
             for (int key = 0; key < g.valid; ++key, ++n) {
@@ -102,14 +104,15 @@ static int walks(int head_dim) {
             for (int f = static_cast<int>(rng() % 5); f < 256 && frames.size() < 1 + rng() % 40; f += 1 + rng() % every)
                 frames.push_back(f);
             const rf::AttnParams p = list(frames, N, 3, head_dim);
-            if (walk<kBc>(p, 0, N >= kBc)) return 1;
+            const int64_t tiles = (p.n_kv * N + kBc - 1) / kBc;
+            const bool saves = N >= kBc && tiles < p.n_kv * ((N + kBc - 1) / kBc);
+            if (walk<kBc>(p, 0, saves)) return 1;
             // the parts that the split plan gives launches of these keys, at tails of any size
             for (int32_t cus : {7, 64, 256})
                 for (int64_t Mq : {int64_t(1), N, 5 * N, 100 * N}) {
                     const rf::AttnSplit sp = rf::attention_split(Mq, p.heads, head_dim, N, p.S, p.n_kv, cus);
                     if (sp.split == 0) continue;
-                    const int64_t tiles = (p.n_kv * N + kBc - 1) / kBc;
-                    if (walk<kBc>(p, sp.split, N >= kBc && tiles > (sp.split - 1) * (sp.split - 1))) return 1;
+                    if (walk<kBc>(p, sp.split, saves && tiles > (sp.split - 1) * (sp.split - 1))) return 1;
                     // the plan's figure, in tiles that do not cross a frame, is the most a part has
                     CHECK((rf::list_walk(p, kBc, sp.split).tiles + sp.split - 1) / sp.split <= sp.kv_per_split);
                 }
@@ -124,7 +127,7 @@ static int guard_on_parts() {
         for (int64_t tiles : {(split - 1) * (split - 1), (split - 1) * (split - 1) + 1}) {
             std::vector<int> frames;   // of 64 keys and a key more: n frames are n tiles up to n = 63
             for (int i = 0; i < tiles - 1; ++i) frames.push_back(2 * i);
-            if (frames.empty()) continue;
+            if (frames.size() < 2) continue;   // (one frame: the same tiles either way)
             const rf::AttnParams p = list(frames, 65, 2, 128);
             const int64_t walked = (static_cast<int64_t>(frames.size()) * 65 + 63) / 64;
             CHECK(walked == tiles);
@@ -142,9 +145,9 @@ static int guard_on_gaps() {
         if (walk<64>(list({0, 1, gap + 2}, 3600, 24, 128), 2, gap <= 97)) return 1;
         if (walk<128>(list({0, gap + 1}, 3600, 48, 64), 0, gap <= 97)) return 1;
     }
-    // exactly at the bound: (gap N + 64) tokens of 256 bytes against 2^31 - 1
-    if (walk<64>(list({0, 2}, 8388607 - 64, 1, 128), 0, true)) return 1;
-    if (walk<64>(list({0, 2}, 8388608 - 64, 1, 128), 0, false)) return 1;
+    // exactly at the bound, and the next above: (3 N + 64) tokens of 256 bytes against 2^31 - 1
+    if (walk<64>(list({0, 4}, 2796181, 1, 128), 0, true)) return 1;
+    if (walk<64>(list({0, 4}, 2796182, 1, 128), 0, false)) return 1;
     return 0;
 }
 
