@@ -143,15 +143,24 @@ def source_digest(path):
     return hashlib.sha256(text.encode()).hexdigest()
 
 
+# The sources that the bf16 attention kernels are compiled from.
+ATTENTION_SOURCES = ("rf_attention.hip", "rf_device.h", "rf_list_walk.h")
+
+
+def attention_digest(csrc=os.path.join(ROOT, "paper_2606_06309_amd", "csrc")):
+    """sha256 over the code digests of ATTENTION_SOURCES."""
+    import hashlib
+    return hashlib.sha256(" ".join(source_digest(os.path.join(csrc, f)) for f in ATTENTION_SOURCES).encode()).hexdigest()
+
+
 def profiled_traffic(workload):
     """HBM bytes per attention launch from the committed rocprofv3 counter
     summary, or None when there is none or the attention code has changed
     since the counters were taken."""
     path = os.path.join(ROOT, "profiles", f"attn_bf16_{workload}_traffic.txt")
-    src = os.path.join(ROOT, "paper_2606_06309_amd", "csrc", "rf_attention.hip")
     if not os.path.exists(path):
         return None
-    sha = source_digest(src)
+    sha = attention_digest()
     fields = {}
     for line in open(path):
         if ":" in line:

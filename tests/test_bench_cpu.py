@@ -3,6 +3,8 @@ without a GPU, the code digest that keys the committed traffic counters, the
 traffic lookup itself, and the guard that keeps a failing side measurement
 from costing the JSON line."""
 import os
+import re
+import shutil
 import subprocess
 import sys
 
@@ -55,13 +57,31 @@ def test_source_digest_ignores_comments_and_whitespace(tmp_path):
     assert bench.source_digest(str(a)) != bench.source_digest(str(c))
 
 
+def test_attention_digest_covers_every_source_of_the_kernels(tmp_path):
+    """The kernel file and the headers of this directory that it includes (rf_internal.h declares host
+    interfaces and argument structs only): a change of code in any of them changes the digest."""
+    csrc = os.path.join(ROOT, "paper_2606_06309_amd", "csrc")
+    included = set(re.findall(r'^#include "(\w+\.h)"', open(os.path.join(csrc, "rf_attention.hip")).read(), re.M))
+    assert {"rf_attention.hip"} | included == set(bench.ATTENTION_SOURCES)
+    for name in bench.ATTENTION_SOURCES:
+        shutil.copy(os.path.join(csrc, name), tmp_path / name)
+    assert bench.attention_digest(str(tmp_path)) == bench.attention_digest()
+    for name in bench.ATTENTION_SOURCES:
+        text = (tmp_path / name).read_text()
+        (tmp_path / name).write_text(text + "// a comment\n")
+        assert bench.attention_digest(str(tmp_path)) == bench.attention_digest()
+        (tmp_path / name).write_text(text + "int more;\n")
+        assert bench.attention_digest(str(tmp_path)) != bench.attention_digest()
+        (tmp_path / name).write_text(text)
+
+
 def test_committed_traffic_is_reported_only_for_the_code_it_was_taken_on():
     """The bench reports the committed counter summary's traffic only while the
     attention code has the digest recorded there (then it exceeds the
     algorithmic bytes); after a change of the code it reports none."""
     path = os.path.join(ROOT, "profiles", "attn_bf16_long_traffic.txt")
     recorded = [l.split(":", 1)[1].strip() for l in open(path) if l.startswith("attention code sha256")]
-    current = bench.source_digest(os.path.join(ROOT, "paper_2606_06309_amd", "csrc", "rf_attention.hip"))
+    current = bench.attention_digest()
     traffic = bench.profiled_traffic("long")
     if recorded == [current]:
         assert isinstance(traffic, int) and traffic > 1813708800
