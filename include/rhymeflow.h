@@ -179,7 +179,8 @@ int rf_keyframe_attention(const void *q, const void *k, const void *v, void *out
  * are cut along the keys into parts that run side by side, and a second small
  * kernel combines each tile's parts (max of the parts' reference maxima,
  * rescaled sums, one bf16 rounding). Rows of split tiles differ from the
- * unsplit result only in fp32 summation order; which tiles are split depends
+ * unsplit result only in fp32 summation order and in the references that their
+ * probabilities are rounded to bf16 against; which tiles are split depends
  * on the launch's size, so the row-for-row bitwise identity between launches
  * of different M that rf_keyframe_attention has does not hold here.
  *
@@ -189,8 +190,8 @@ int rf_keyframe_attention(const void *q, const void *k, const void *v, void *out
  *   contents are overwritten and meaningless afterwards. fp32 needs and
  *   touches none of it, but a small launch (of either type) given one shares
  *   out the keys of each query tile among the waves of a workgroup instead of
- *   splitting a tail (the same effect on the order of its sums) and leaves the
- *   workspace alone.
+ *   splitting a tail (with the same effect on its results) and leaves the
+ *   workspace alone (rf_attention_plan's shared_keys).
  * Other arguments and errors as rf_keyframe_attention; RF_ERR_INVALID_ARG also
  * for a NULL or too small workspace or an overlap.
  */

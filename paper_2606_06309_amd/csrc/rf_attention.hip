@@ -110,8 +110,10 @@ constexpr int kBr = 32 * kWaves;   // query rows per workgroup
 // hold them).
 __host__ __device__ constexpr int key_tile(int head_dim) { return head_dim == 64 ? RF_ATTN_BC64 : RF_ATTN_BC; }
 // Split-key tail: the most parts a tail tile is cut into and the fewest key
-// tiles a part may have. A round of whole tiles fills the device's compute
-// units (one workgroup per CU), queried at launch.
+// tiles a part has by the plan, which counts a frame list's tiles without any that
+// crosses a frame (walked end to end there may be about half as many, and a part
+// is that much shorter; list_walk sees to it that none is empty). A round of whole
+// tiles fills the device's compute units (one workgroup per CU), queried at launch.
 constexpr int kMaxSplit = 8;
 constexpr int kMinKvPerSplit = 8;
 constexpr float kRebaseBound = RF_ATTN_REBASE_BOUND;   // largest tile row sum kept without a rebase
@@ -697,7 +699,9 @@ void attn_bf16_kernel(const AttnKArgs a) {
 // take; a launch that leaves most CUs idle in 256-row tiles has that to spare.
 // Kernel and combine against this one: 9 frames of 17 x 31, 5 heads x 64, three
 // keyframes 31.1 -> 19.0 us (504 TFLOP/s); 13 of 16 x 16, 8 x 64, four 27.1 ->
-// 15.6; 9 of 10 x 13, 3 x 128, three 24.5 -> 11.5.
+// 15.6; 9 of 10 x 13, 3 x 128, three 24.5 -> 11.5. 182 vector registers at head
+// dimension 128, 166 at 64, where the compiler also spills 6 scalar registers (14
+// with a frame list) to vector lanes.
 // ---------------------------------------------------------------------------
 
 constexpr int kSmallRows = 32;
@@ -1006,7 +1010,7 @@ AttnSplit attention_split(int64_t Mq, int32_t heads, int32_t head_dim, int64_t N
     sp.n_direct = total - tail;
     sp.n_tail = tail;
     sp.split = best_s;
-    // a frame-aligned walk has at least as many key tiles, so its parts keep >= kMinKvPerSplit
+    // (the cache form's frame-aligned walk has at least kv_tiles tiles: its parts keep kMinKvPerSplit)
     const int64_t walk = walk_frames > 0 ? static_cast<int64_t>(walk_frames) * ((N + kBc - 1) / kBc) : kv_tiles;
     sp.kv_per_split = (walk + best_s - 1) / best_s;
     sp.ws_bytes = tail * best_s * kBr * (static_cast<int64_t>(head_dim) * 4 + 8);
