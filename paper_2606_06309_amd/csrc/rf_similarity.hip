@@ -390,12 +390,13 @@ SimGeometry similarity_geometry(int32_t B, int32_t C, int32_t T, int64_t plane) 
     // 90 x 160: 17.8 us against 18.8; 48 frames: 24.8 against 31.3). Where a wave
     // then walks more than kLongWalk chunks its loads and its matrix instructions add
     // up, and two workgroups overlap them as long as the registers hold two waves a
-    // SIMD, that is up to 44 frames in fp32 and 48 in bf16 (one against two, 16 x 90 x
-    // 160; 33 frames, fp32: 36 videos 272 us, 236; 12: 97.6, 88.7; 5, 17.6 chunks: 46.5,
-    // 45.2; 2, 7 chunks: 25.8, 27.0; 40 frames: 5 videos 53.6, 52.4; 20: 188, 165; bf16
-    // 49.0, 47.9; 186, 163; 44: 61.3, 59.7; 215, 192; bf16 55.9, 54.5; 213, 188; 48: fp32
-    // 68.3, 76.0; 243, 244; bf16 63.6, 62.7; 243, 215). Two are taken up to 36 frames;
-    // 37 to 44, and to 48 in bf16, keep one for the present, 2-12 % above two.
+    // SIMD, that is up to 44 frames in fp32 and 48 in bf16 (one against two, many calls
+    // back to back over two sets of buffers, 16 x 90 x 160; 33 frames, fp32: 36 videos
+    // 272 us, 236; 12: 97.6, 88.7; 5, 17.6 chunks: 46.5, 45.2; 2, 7 chunks: 25.8, 27.0; 40
+    // frames: 5 videos 53.6, 52.4; 20: 188, 165; bf16 49.0, 47.9; 186, 163; 44: 61.3, 59.7;
+    // 215, 192; bf16 55.9, 54.5; 213, 188; 48: fp32 68.3, 76.0; 243, 244; bf16 63.6, 62.7;
+    // 243, 215). Two are taken up to 36 frames; 37 to 44, and to 48 in bf16, keep one for
+    // the present, 2-12 % above two.
     constexpr int64_t kLongWalk = 16;
     const int64_t one_per_cu = kMaxWorkgroups / 2 / B > 0 ? kMaxWorkgroups / 2 / B : 1;
     const bool long_walk = g.NB <= 9 && g.n_chunks * B > kLongWalk * (kMaxWorkgroups / 2) * (kThreads / 64);
