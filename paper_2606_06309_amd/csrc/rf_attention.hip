@@ -284,6 +284,18 @@ __device__ __forceinline__ void pv_tile(const uint8_t *vb, const int (&vofs)[D /
     __builtin_amdgcn_sched_group_barrier(0x008, kLead, 0);
 }
 
+// The reference of a row's rebased tile (log2 domain): its running maximum so far,
+// of which mx is this tile's. Probabilities are exp2(fma(score, scale, -reference)),
+// so where the rounding of mx * scale is worth 2^6 and more (from about 2^31 on, where
+// the largest score itself would give inf or 0), and where every score is -inf, the
+// reference is at least -2^30: such low scores then give 0, and the next tile that
+// has an ordinary one rebases the row. A walk over the keys, or a part of one, may
+// begin with whole tiles of them.
+__device__ __forceinline__ float rebased_reference(float m_run, float mx, float sl2) {
+    const float m = mx * sl2, m_new = fmaxf(m_run, m);
+    return fabsf(fmaf(mx, sl2, -m)) < 64.0f ? m_new : fmaxf(m_new, -0x1p30f);
+}
+
 // Query fragments: B operand of S^T = K Q^T (fused keyframe gather).
 template <int D>
 __device__ __forceinline__ void load_queries(const AttnKArgs &a, int64_t row, int head, int grp,
@@ -600,20 +612,15 @@ void attn_bf16_kernel(const AttnKArgs a) {
             for (int b = 0; b < kNB; ++b)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[b][r]);
-            const float m_new = fmaxf(m_run, halves_max(mx) * sl2);
-            // a row whose scores so far are all -inf (the first tiles of the walk, or of a
-            // part of the split tail) takes 0 as its reference for this tile: its
-            // probabilities are 0 and the next tile rebases it
-            const float ref = m_new == -__builtin_huge_valf() ? 0.0f : m_new;
-            const float corr = fast_exp2(m_run - ref);   // 0 on the first tile
-            m_run = ref;
+            const float m_new = rebased_reference(m_run, halves_max(mx), sl2);
+            const float corr = fast_exp2(m_run - m_new);   // 0 on the first tile
+            m_run = m_new;
             l_run *= corr;
 #pragma unroll
             for (int db = 0; db < D / 32; ++db)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) oacc[db][r] *= corr;
             ls = probs();
-            m_run = m_new;
         }
         l_run += ls;
 
@@ -742,19 +749,15 @@ __device__ __forceinline__ void softmax_tile(f32x16_t (&sacc)[kNB], int32_t vali
         for (int b = 0; b < kNB; ++b)
 #pragma unroll
             for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[b][r]);
-        const float m_new = fmaxf(m_run, halves_max(mx) * sl2);
-        // a row whose scores so far are all -inf takes 0 as its reference for this tile:
-        // its probabilities are 0 and the wave's next tile rebases it
-        const float ref = m_new == -__builtin_huge_valf() ? 0.0f : m_new;
-        const float corr = fast_exp2(m_run - ref);
-        m_run = ref;
+        const float m_new = rebased_reference(m_run, halves_max(mx), sl2);
+        const float corr = fast_exp2(m_run - m_new);
+        m_run = m_new;
         l_run *= corr;
 #pragma unroll
         for (int db = 0; db < D / 32; ++db)
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[db][r] *= corr;
         ls = probs();
-        m_run = m_new;
     }
     l_run += ls;
 }
